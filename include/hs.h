@@ -177,9 +177,14 @@ typedef struct hs_plan_opts {
  * in decreasing order, then one wave-level reverse pointer jumping per
  * block over the seeds and the anchors' inflows (tiles whose anchors do not
  * fit the LDS fall back to HS_ADJ_ROUNDS).  HS_ADJ_AUTO resolves per call:
- * HS_ADJ_ANCHORS for end-effector seeds, HS_ADJ_ROUNDS for a dense
- * dLoss/dG (measured fastest for each: on a dense seed every joint of a
- * chain block sends to one anchor).  Given checkpoints, characters of up
+ * the path adjoint -- every tree cut into pieces of paths, one piece per
+ * thread, pointer jumping over the pieces only; it has no bounded waits --
+ * for a dense dLoss/dG, and for end-effector seeds once the tiles of
+ * HS_ADJ_ANCHORS would not all be resident at once (HS_ADJ_ANCHORS until
+ * then); where the path adjoint does not apply (a character of more than
+ * 512 pieces, more than 64 pieces below one joint, or a wait limit of zero)
+ * HS_ADJ_ANCHORS for end-effector seeds and HS_ADJ_ROUNDS for a dense
+ * dLoss/dG.  Given checkpoints, characters of up
  * to 1664 joints always run the dataflow kernel, which rebuilds each G_j
  * from them. */
 #define HS_ADJ_AUTO 0

@@ -5,15 +5,19 @@
 #include "hs_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
+#include <unordered_map>
 #include <vector>
 
 static_assert(hs::kNoAllocMaxJoints == HS_NOALLOC_MAX_JOINTS, "static workspace size");
@@ -98,6 +102,43 @@ hipError_t fetch(std::vector<T> &dst, const T *src, size_t n)
         return hipSuccess;
     }
     return hipMemcpy(dst.data(), src, n * sizeof(T), hipMemcpyDeviceToHost);
+}
+
+// f(begin, end) over pieces of [0, n), on up to eight threads when there is
+// enough to do (`work`, in joints).  The pieces are independent; what a piece
+// throws is thrown again here, and if no thread can be started the calling
+// one does everything.
+template <class F>
+void parallel_pieces(int64_t n, int64_t work, F f)
+{
+    const int64_t most = std::min<int64_t>({8, (int64_t)std::thread::hardware_concurrency(), work >> 16, n});
+    if (most < 2) {
+        if (n > 0) f((int64_t)0, n);
+        return;
+    }
+    const int64_t piece = std::max<int64_t>(1, n / (8 * most));
+    std::atomic<int64_t> next{0};
+    std::exception_ptr thrown;
+    std::mutex mu;
+    auto worker = [&]() {
+        try {
+            for (int64_t b; (b = next.fetch_add(piece)) < n;) f(b, std::min(n, b + piece));
+        } catch (...) {
+            std::lock_guard<std::mutex> lk(mu);
+            if (!thrown) thrown = std::current_exception();
+            next = n;
+        }
+    };
+    std::vector<std::thread> pool;
+    try {
+        pool.reserve((size_t)most - 1);
+        for (int64_t i = 1; i < most; ++i) pool.emplace_back(worker);
+    } catch (...) {
+        // fewer threads than asked for
+    }
+    worker();
+    for (std::thread &t : pool) t.join();
+    if (thrown) std::rethrow_exception(thrown);
 }
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -422,7 +463,19 @@ struct hs_plan {
     bool b_anchor_ok = false;    // the two-level adjoint fits the LDS
     int b_bpw_opt = 0;           // the two-level adjoint's blocks per wave as asked (0 = choose)
     int b_bpw[3] = {1, 1, 1};    // ... as chosen, per seed kind (dense, effectors, forward in the tile)
+    bool b_one_round[3] = {false, false, false};  // with one block per wave every tile is resident at once
     int64_t bwd_untiled = 0;  // joints the adjoint's tiles do not cover
+    // the path adjoint over the same characters as d_btiles (num_tiles = 0:
+    // the plan asked for another kernel, or the characters do not suit it)
+    struct PathSet {
+        char *d_tables = nullptr;  // one allocation: tiles, lanes, steps, slots
+        const hs::PathTile *d_tiles = nullptr;
+        const hs::PathLane *d_lanes = nullptr;
+        const uint32_t *d_steps = nullptr;
+        const uint16_t *d_slot = nullptr;
+        std::vector<hs::PathTile> h_tiles;
+        int32_t threads = 0, max_lanes = 0, max_rows = 0, max_count = 0;
+    } paths;
     int32_t max_units = 0;
     // multipass: characters larger than the forward tile (mp) and than the
     // adjoint tile (bmp, with the adjoint workspace)
@@ -452,6 +505,12 @@ struct hs_plan {
 
 namespace {
 
+void free_paths(hs_plan::PathSet &ps)
+{
+    (void)hipFree(ps.d_tables);
+    ps = hs_plan::PathSet{};
+}
+
 void free_plan(hs_plan *p)
 {
     if (!p) return;
@@ -470,6 +529,7 @@ void free_plan(hs_plan *p)
     (void)hipFree(p->q.d_tiles);
     (void)hipFree(p->q.d_code);
     (void)hipFree(p->d_bcode);
+    free_paths(p->paths);
     delete p;
 }
 
@@ -863,6 +923,312 @@ int tile_codes(const hs_plan *plan, const TileDesc &t, std::vector<int32_t> &cod
     return na;
 }
 
+// tile_codes of every tile; returns their anchor counts.
+std::vector<int> all_tile_codes(const hs_plan *plan, const std::vector<TileDesc> &tiles, std::vector<int32_t> &code)
+{
+    std::vector<int> na(tiles.size());
+    parallel_pieces((int64_t)tiles.size(), plan->N, [&](int64_t b, int64_t e) {
+        std::vector<int32_t> slot;
+        for (int64_t i = b; i < e; ++i) na[i] = tile_codes(plan, tiles[i], code, slot);
+    });
+    return na;
+}
+
+// The path adjoint's tiles (hs_internal.h, PathTile): every character of up
+// to kMaxSyncTileJoints joints in pieces of paths.  A path goes from its head
+// to the child with the most levels below it, so that the longest paths stay
+// whole, and is cut every kPathLen joints.  Builds nothing where some
+// character has more than kPathMaxLanes pieces (a thread each) or a joint more
+// than kPathMaxFanIn pieces below it (one thread adds them): stars and the
+// like, where few rounds of the synchronous kernel do.
+// The pieces of one character (parents pa, n joints): each joint's piece,
+// counted from 0, and its place in it.  Returns their number, or -1 when too
+// many lie below one joint.
+int cut_paths(const int32_t *pa, int64_t n, int16_t *lane, uint8_t *pos, std::vector<int16_t> &height,
+              std::vector<int16_t> &best, std::vector<int16_t> &fan)
+{
+    height.assign((size_t)n, 1);
+    best.assign((size_t)n, -1);
+    fan.assign((size_t)n, 0);
+    for (int64_t j = n - 1; j > 0; --j) {
+        const int32_t p = pa[j];
+        if (p >= 0 && height[j] + 1 >= height[p]) {  // the first of the deepest children
+            height[p] = (int16_t)(height[j] + 1);
+            best[p] = (int16_t)j;
+        }
+    }
+    int pieces = 0;
+    for (int64_t j = 0; j < n; ++j) {
+        const int32_t p = pa[j];
+        const int at = p >= 0 && best[p] == j ? (pos[p] + 1) % hs::kPathLen : 0;
+        pos[j] = (uint8_t)at;
+        lane[j] = at == 0 ? (int16_t)pieces++ : lane[p];
+        if (at == 0 && p >= 0 && ++fan[p] > hs::kPathMaxFanIn) return -1;
+    }
+    return pieces;
+}
+
+// One tile's tables: characters c .. e - 1 (t.begin, count and lanes are
+// set); slot and pl: its joints' rows and its lanes.  The step words go to
+// `steps`.
+void fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e, const std::vector<int32_t> &pieces,
+                    const int16_t *lane, const uint8_t *pos, uint16_t *slot, hs::PathLane *pl,
+                    std::vector<uint32_t> &steps)
+{
+    constexpr int K = hs::kPathLen;
+    const auto &off = plan->h_offsets;
+    const auto &par = plan->h_parents;
+    const size_t nl = (size_t)t.lanes;
+    std::vector<int> len(nl, 0), place(nl, 0), depth(nl, 1), first_branch(nl, 0), nbr(nl, 0);
+    std::vector<int32_t> head_parent(nl, -1);                // tile-local joint above the lane's head
+    std::vector<int16_t> branch_of((size_t)t.count, -1);     // a branch's number in its lane
+    int deepest = 1, base = 0;
+    for (int64_t k = c; k < e; ++k) {
+        const int64_t o = off[k];
+        for (int64_t g = o; g < off[k + 1]; ++g) {
+            const int l = base + lane[g];
+            ++len[l];
+            if (pos[g] == 0 && par[g] >= 0) {
+                head_parent[l] = (int32_t)(o - t.begin) + par[g];
+                branch_of[head_parent[l]] = 0;
+                depth[l] = depth[base + lane[o + par[g]]] + 1;
+                deepest = std::max(deepest, depth[l]);
+            }
+        }
+        base += pieces[k];
+    }
+    t.rounds = ceil_log2(deepest);
+    // lanes by length, longest first (those of one length in joint order)
+    int count_of[K + 1] = {0}, at[K + 1] = {0};
+    for (size_t l = 0; l < nl; ++l) ++count_of[len[l]];
+    for (int k = K, longer = 0; k >= 1; longer += count_of[k--]) at[k] = longer;
+    for (size_t l = 0; l < nl; ++l) place[l] = at[len[l]]++;
+    // rows: step after step, an odd stride between them so that a path's
+    // joints (one lane, step after step) fall on different LDS banks
+    int row = 0;
+    for (int k = 0, more = (int)nl; k < K; ++k) {
+        t.start[k] = row;
+        row += more > 0 ? more | 1 : 0;
+        more -= count_of[k + 1];
+    }
+    t.rows = row;
+    // branches, lane by lane in the sorted order, in joint order in a lane
+    for (size_t i = 0; i < nl; ++i) pl[i] = hs::PathLane{0, 0, 0, 0};
+    base = 0;
+    for (int64_t k = c; k < e; ++k) {
+        for (int64_t g = off[k]; g < off[k + 1]; ++g) {
+            const int l = place[base + lane[g]];
+            slot[g - t.begin] = (uint16_t)(t.start[pos[g]] + l);
+            if (branch_of[g - t.begin] >= 0) {
+                branch_of[g - t.begin] = (int16_t)nbr[l]++;
+                pl[l].down |= 1 << pos[g];
+            }
+        }
+        base += pieces[k];
+    }
+    for (size_t i = 0, b = 0; i < nl; b += nbr[i++]) {
+        first_branch[i] = (int)b;
+        pl[i].down |= (int)b << 8;
+    }
+    std::vector<int> up(nl, -1);
+    base = 0;
+    for (int64_t k = c; k < e; ++k) {
+        for (int q = 0; q < pieces[k]; ++q) {
+            const int l = place[base + q];
+            pl[l].up = len[base + q] << 16;
+            const int32_t hp = head_parent[base + q];
+            if (hp < 0) continue;
+            up[l] = place[base + lane[t.begin + hp]];
+            pl[l].up |= up[l] + 1;
+            pl[l].from = first_branch[up[l]] + branch_of[hp] + 1;
+            pl[up[l]].kids += 1u << 8 * pos[t.begin + hp];
+        }
+        base += pieces[k];
+    }
+    // the rounds' rows: the senders sorted by branch in the first one, by the
+    // lane they reach in the others
+    std::vector<int> next(nl), first, count(nl), row_of(nl);
+    for (int r = 0; r < t.rounds; ++r) {
+        first.assign(nl + 1, 0);
+        std::fill(count.begin(), count.end(), 0);
+        for (size_t l = 0; l < nl; ++l)
+            if (up[l] >= 0) {
+                ++count[up[l]];
+                ++first[(r == 0 ? pl[l].from - 1 : up[l]) + 1];
+            }
+        for (size_t i = 0; i < nl; ++i) first[i + 1] += first[i];
+        for (size_t l = 0; l < nl; ++l) row_of[l] = up[l] >= 0 ? first[r == 0 ? pl[l].from - 1 : up[l]]++ : 0;
+        for (size_t l = 0, sum = 0; l < nl; sum += count[l++])
+            steps.push_back(hs::path_step((uint32_t)row_of[l], (uint32_t)sum, (uint32_t)count[l]));
+        for (size_t l = 0; l < nl; ++l) next[l] = up[l] >= 0 ? up[up[l]] : -1;
+        up.swap(next);
+    }
+}
+
+hs_status build_paths(hs_plan *plan)
+{
+    auto &P = plan->paths;
+    free_paths(P);
+    constexpr int K = hs::kPathLen;
+    const auto &off = plan->h_offsets;
+    const int64_t C = plan->C, N = plan->N;
+    std::vector<int16_t> lane((size_t)N);  // piece of each joint, counted in its character
+    std::vector<uint8_t> pos((size_t)N);   // place in the piece
+    std::vector<int32_t> pieces((size_t)C, 0);
+    std::atomic<bool> fits{true};
+    parallel_pieces(C, N, [&](int64_t b, int64_t e) {
+        std::vector<int16_t> height, best, fan;
+        for (int64_t c = b; c < e && fits; ++c) {
+            const int64_t o = off[c], n = off[c + 1] - o;
+            if (n == 0 || n > hs::kMaxSyncTileJoints) continue;
+            pieces[c] = cut_paths(plan->h_parents.data() + o, n, lane.data() + o, pos.data() + o, height, best, fan);
+            if (pieces[c] < 0 || pieces[c] > hs::kPathMaxLanes) fits = false;
+        }
+    });
+    if (!fits) return HS_OK;
+    int64_t total = 0;
+    int most = 0;
+    for (int64_t c = 0; c < C; ++c) {
+        total += pieces[c];
+        most = std::max(most, pieces[c]);
+    }
+    if (total == 0) return HS_OK;
+    // A workgroup has a thread for every lane of the largest character, and
+    // smaller characters share one of up to 256 threads while that leaves four
+    // workgroups per CU (10 000 x 256 joints, 76 lanes each: 96 us with 256
+    // threads, 113 with 128).
+    const int64_t nc = std::max(1, plan->ctx->num_cu);
+    const int64_t spread = (total + 4 * nc - 1) / (4 * nc);
+    const int cap_lanes = (int)std::max<int64_t>(most, std::min<int64_t>(256, spread));
+    P.threads = round_up(cap_lanes, 64);
+    const int cap_joints = std::min(K * P.threads, hs::kMaxSyncTileJoints);
+
+    std::vector<hs::PathTile> tiles;
+    std::vector<std::pair<int64_t, int64_t>> chars;  // of each tile
+    for (int64_t c = 0; c < C;) {
+        if (pieces[c] == 0) {
+            ++c;
+            continue;
+        }
+        hs::PathTile t{};
+        t.begin = off[c];
+        int64_t e = c;
+        for (; e < C; ++e) {  // whole characters, of consecutive ids
+            const int64_t n = off[e + 1] - off[e];
+            if (n > hs::kMaxSyncTileJoints ||
+                (t.count > 0 && (t.count + n > cap_joints || t.lanes + pieces[e] > cap_lanes)))
+                break;
+            t.count += (int32_t)n;
+            t.lanes += pieces[e];
+        }
+        tiles.push_back(t);
+        chars.emplace_back(c, e);
+        c = e;
+    }
+    // Tiles of the same characters (crowds of one skeleton) share their tables:
+    // `same[i]` is the first tile like tile i.  Two tiles are alike when their
+    // characters' sizes and parents are.
+    const size_t nt = tiles.size();
+    const int32_t *par = plan->h_parents.data();
+    std::vector<uint64_t> hash(nt);
+    parallel_pieces((int64_t)nt, N, [&](int64_t b, int64_t e) {
+        for (int64_t i = b; i < e; ++i) {
+            uint64_t h = 1469598103934665603u;
+            auto mix = [&](uint32_t v) { h = (h ^ v) * 1099511628211u; };
+            for (int64_t c = chars[i].first; c < chars[i].second; ++c) mix((uint32_t)(off[c + 1] - off[c]));
+            for (int32_t j = 0; j < tiles[i].count; ++j) mix((uint32_t)par[tiles[i].begin + j]);
+            hash[i] = h;
+        }
+    });
+    auto alike = [&](size_t i, size_t k) {
+        if (tiles[i].count != tiles[k].count || chars[i].second - chars[i].first != chars[k].second - chars[k].first)
+            return false;
+        for (int64_t c = chars[i].first, d = chars[k].first; c < chars[i].second; ++c, ++d)
+            if (off[c + 1] - off[c] != off[d + 1] - off[d]) return false;
+        return std::memcmp(par + tiles[i].begin, par + tiles[k].begin, (size_t)tiles[i].count * sizeof(int32_t)) == 0;
+    };
+    std::vector<size_t> same(nt), own;
+    std::unordered_map<uint64_t, size_t> seen;  // a hash's first tile
+    int64_t used_lanes = 0, used_slots = 0;
+    for (size_t i = 0; i < nt; ++i) {
+        const auto at = seen.emplace(hash[i], i).first;
+        same[i] = at->second != i && alike(i, at->second) ? at->second : i;
+        if (same[i] != i) continue;
+        own.push_back(i);
+        tiles[i].lane_begin = (int32_t)used_lanes;
+        tiles[i].slot_begin = (int32_t)used_slots;
+        used_lanes += tiles[i].lanes;
+        used_slots += tiles[i].count;
+    }
+    std::vector<hs::PathLane> lanes((size_t)used_lanes);
+    std::vector<uint16_t> slot((size_t)used_slots);
+    std::vector<std::vector<uint32_t>> tile_steps(nt);
+    parallel_pieces((int64_t)own.size(), used_slots, [&](int64_t b, int64_t e) {
+        for (int64_t k = b; k < e; ++k) {
+            const size_t i = own[k];
+            fill_path_tile(plan, tiles[i], chars[i].first, chars[i].second, pieces, lane.data(), pos.data(),
+                           slot.data() + tiles[i].slot_begin, lanes.data() + tiles[i].lane_begin, tile_steps[i]);
+        }
+    });
+    size_t words = 0;
+    for (size_t i : own) words += tile_steps[i].size();
+    std::vector<uint32_t> steps(words);
+    words = 0;
+    for (size_t i = 0; i < nt; ++i) {
+        hs::PathTile &t = tiles[i];
+        if (same[i] == i) {
+            t.step_begin = (int32_t)words;
+            std::copy(tile_steps[i].begin(), tile_steps[i].end(), steps.begin() + (ptrdiff_t)words);
+            words += tile_steps[i].size();
+        } else {
+            const int64_t begin = t.begin;
+            t = tiles[same[i]];
+            t.begin = begin;
+        }
+        P.max_lanes = std::max(P.max_lanes, t.lanes);
+        P.max_rows = std::max(P.max_rows, t.rows);
+        P.max_count = std::max(P.max_count, t.count);
+    }
+    if (hs::backward_path_lds_bytes(P.max_lanes, P.max_rows, P.max_count, true) > plan->ctx->max_lds ||
+        steps.size() > (size_t)INT32_MAX)
+        return HS_OK;
+    std::stable_sort(tiles.begin(), tiles.end(),
+                     [](const hs::PathTile &a, const hs::PathTile &b) { return a.count > b.count; });
+    // tiles (64 bytes each), lanes (16), steps (4), slots (2): in this order each is aligned
+    const size_t at_lanes = tiles.size() * sizeof(tiles[0]), at_steps = at_lanes + lanes.size() * sizeof(lanes[0]),
+                 at_slot = at_steps + steps.size() * sizeof(steps[0]);
+    std::vector<char> all(at_slot + slot.size() * sizeof(slot[0]));
+    std::memcpy(all.data(), tiles.data(), at_lanes);
+    std::memcpy(all.data() + at_lanes, lanes.data(), at_steps - at_lanes);
+    if (at_slot > at_steps) std::memcpy(all.data() + at_steps, steps.data(), at_slot - at_steps);
+    std::memcpy(all.data() + at_slot, slot.data(), all.size() - at_slot);
+    hipError_t err = upload(&P.d_tables, all);
+    if (err != hipSuccess) return fail_hip(err, "hs_plan_create (path adjoint)");
+    P.d_tiles = reinterpret_cast<const hs::PathTile *>(P.d_tables);
+    P.d_lanes = reinterpret_cast<const hs::PathLane *>(P.d_tables + at_lanes);
+    P.d_steps = reinterpret_cast<const uint32_t *>(P.d_tables + at_steps);
+    P.d_slot = reinterpret_cast<const uint16_t *>(P.d_tables + at_slot);
+    P.h_tiles.swap(tiles);
+    return HS_OK;
+}
+
+hs::PathLaunch path_launch(const hs_plan *p, bool validate)
+{
+    const auto &P = p->paths;
+    hs::PathLaunch pl{};
+    pl.tiles = P.d_tiles;
+    pl.num_tiles = (int32_t)P.h_tiles.size();
+    pl.threads = P.threads;
+    pl.max_lanes = P.max_lanes;
+    pl.max_rows = P.max_rows;
+    pl.max_count = P.max_count;
+    pl.lanes = P.d_lanes;
+    pl.steps = P.d_steps;
+    pl.slot = P.d_slot;
+    pl.gate = validate ? p->d_status : nullptr;
+    return pl;
+}
+
 hs_status build_queue(hs_plan *plan, const Shape &shape, int strategy, bool *built)
 {
     *built = false;
@@ -875,11 +1241,12 @@ hs_status build_queue(hs_plan *plan, const Shape &shape, int strategy, bool *bui
     const int cap = shape.queue_cap > 0 ? shape.queue_cap : shape.tile_cap;
     const Packing pk = pack_tiles(plan, cap, strategy, false, 0, cap);
     std::vector<hs::QTile> qt(pk.tiles.size());
-    std::vector<int32_t> code((size_t)plan->N, 0), slot;
+    std::vector<int32_t> code((size_t)plan->N, 0);
+    const std::vector<int> anchors = all_tile_codes(plan, pk.tiles, code);
     int max_anchors = 0;
     for (size_t i = 0; i < pk.tiles.size(); ++i) {
         const TileDesc &t = pk.tiles[i];
-        const int na = tile_codes(plan, t, code, slot);
+        const int na = anchors[i];
         hs::QTile &q = qt[i];
         q = hs::QTile{};
         q.begin = t.begin;
@@ -994,9 +1361,8 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
         plan->b_max_anchors = 0;
         plan->b_anchor_ok = false;
         if (!ps.tiles.empty()) {
-            std::vector<int32_t> code((size_t)plan->N, 0), slot;
-            for (const TileDesc &t : ps.tiles)
-                plan->b_max_anchors = std::max(plan->b_max_anchors, tile_codes(plan, t, code, slot));
+            std::vector<int32_t> code((size_t)plan->N, 0);
+            for (int na : all_tile_codes(plan, ps.tiles, code)) plan->b_max_anchors = std::max(plan->b_max_anchors, na);
             int w = 1;
             while (w * 64 < plan->bwd_cap) w *= 2;
             const size_t lds1 = hs::backward_anchor_lds_bytes(w, plan->b_max_anchors, plan->bwd_cap);
@@ -1019,6 +1385,7 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
                 if (plan->b_bpw_opt == 1 && occ1 > 0) bpw = 1;
                 if (bpw == 1 && occ1 == 0) plan->b_anchor_ok = false;
                 plan->b_bpw[kind] = bpw;
+                plan->b_one_round[kind] = r1 == 1;
             }
             hipError_t e3 = upload(&plan->d_bcode, code);
             if (e3 != hipSuccess) return fail_hip(e3, "hs_plan_create (adjoint codes)");
@@ -1763,12 +2130,12 @@ hs_status create_plan(hs_context *ctx, const hs_batch *batch, const hs_plan_opts
         const int wmax = sh.tile_cap <= 1024 ? 8 : 16;
         int w = 1;
         while (w * 2 <= std::min(wmax, plan->max_units)) w *= 2;
-        if (w != sh.waves) {
-            sh.waves = w;
-            rc = build_tables(plan, sh, o.strategy);
-        }
+        // (no table depends on it)
+        sh.waves = plan->shape.waves = w;
+        if (plan->info.schedule == HS_SCHED_CLASSES) plan->info.waves_per_tile = w;
     }
     if (rc == HS_OK && o.autotune && N > 0 && sh.algorithm == HS_ALG_SCAN) rc = autotune(plan, sh, o.strategy);
+    if (rc == HS_OK && o.adjoint == HS_ADJ_AUTO && o.strategy != HS_STRATEGY_MULTIPASS) rc = build_paths(plan);
     if (rc == HS_OK && plan->inst && (plan->mp.nmp > 0 || plan->mp.chain_joints > 0))
         rc = fail(HS_ERR_UNSUPPORTED, "instanced plans need every character on a tile (%d joints at most here)",
                   plan->shape.tile_cap);
@@ -2141,10 +2508,11 @@ void free_mesh(hs_mesh *m)
 
 namespace {
 
-// The adjoint's launches: synchronous-round (or dataflow) tiles, the large
-// dataflow tiles, then the multipass characters.
+// The adjoint's launches: path tiles (or the synchronous-round, two-level or
+// dataflow ones), the large dataflow tiles, then the multipass characters.
+// eff_path_tile: the effector set's ranges by path tile (sparse seeds).
 hs_status run_backward(const hs_plan *plan, const hs::PoseArgs &pa, const hs::BwdArgs &ba, hipStream_t stream,
-                       const char *what, bool validate = false)
+                       const char *what, bool validate = false, const int32_t *eff_path_tile = nullptr)
 {
     if (validate) {
         hs_status rc = launch_validate(plan, stream, what);
@@ -2153,7 +2521,24 @@ hs_status run_backward(const hs_plan *plan, const hs::PoseArgs &pa, const hs::Bw
     hs::TileLaunch tl = tile_launch(plan, -1, validate);
     tl.chain_units = 0;
     hipError_t err = hipSuccess;
-    if (plan->num_btiles > 0) {
+    const int kind = ba.eff_ids ? (ba.eff_forward ? 2 : 1) : 0;
+    // The path adjoint does a third of the others' work, but one tile takes it
+    // longer than the two-level kernel with a wave for every block.  So while
+    // every tile of the latter is resident at once it serves end-effector seeds
+    // (steps of 512 x 512 joints: 21.3 against 22.0 us, 200 x 512: 16.3 against
+    // 18.3), the path adjoint beyond (640 x 512: 23.9 against 28.2, 1024 x 512:
+    // 26.5 against 33.7) and always for dense seeds (2048 characters of 32 to
+    // 1024 joints: 54 against 118 us in the synchronous rounds, 10 000 x 256
+    // joints: 96 against 170).  It has no bounded waits: a plan whose waits are
+    // to give up at once (a limit of zero polls) runs the kernels that wait.
+    const bool paths = !plan->paths.h_tiles.empty() && !ba.ckpt && plan->spin_limit > 0 &&
+                       (kind == 0 || !plan->b_anchor_ok || !plan->b_one_round[kind]);
+    if (paths) {
+        hs::BwdArgs pb = ba;
+        if (ba.eff_ids) pb.eff_tile = eff_path_tile;
+        err = hs::launch_backward_paths(path_launch(plan, validate), pa, pb, stream);
+        if (err != hipSuccess) return fail_hip(err, (std::string(what) + " (paths)").c_str());
+    } else if (plan->num_btiles > 0) {
         tl.tiles = plan->d_btiles;
         tl.num_tiles = plan->num_btiles;
         tl.tile_cap = plan->bwd_cap;
@@ -2161,15 +2546,15 @@ hs_status run_backward(const hs_plan *plan, const hs::PoseArgs &pa, const hs::Bw
         // nearest checkpointed ancestor; without, the plan's kernel
         // recomputes them (the synchronous rounds: as their jump products)
         tl.adjoint = ba.ckpt ? hs::kAdjDataflow : plan->shape.adjoint;
-        // AUTO: the two-level kernel for end-effector seeds (measured on
-        // the differentiable workload: 40 against 49 us per step), the
+        // AUTO, off the path adjoint: the two-level kernel for end-effector
+        // seeds (1024 x 512 joints: 40 against 49 us per step), the
         // synchronous rounds for dense seeds (37 against 73 us: every joint
         // of a chain block sends to the same anchor)
         if (tl.adjoint == 0) tl.adjoint = ba.eff_ids ? hs::kAdjAnchors : hs::kAdjRounds;
         if (tl.adjoint == hs::kAdjAnchors && !plan->b_anchor_ok) tl.adjoint = hs::kAdjRounds;
         tl.code = plan->d_bcode;
         tl.max_anchors = plan->b_max_anchors;
-        tl.blocks_per_wave = plan->b_bpw[ba.eff_ids ? (ba.eff_forward ? 2 : 1) : 0];
+        tl.blocks_per_wave = plan->b_bpw[kind];
         tl.grid = plan->num_btiles;
         tl.waves = 1;  // dataflow: a power of two, at most one wave per block
         while (tl.waves < 16 && tl.waves * 2 * 64 <= plan->bwd_cap) tl.waves *= 2;
@@ -2386,6 +2771,7 @@ struct hs_effectors {
     int64_t *d_ids = nullptr;   // ascending (sparse) or in the caller's order (dense)
     int32_t *d_row = nullptr;   // target row of each sorted id
     int32_t *d_tile = nullptr;  // [num_btiles][2]: each tile's range of d_ids
+    int32_t *d_ptile = nullptr; // the same by tile of the path adjoint
     float *d_dense = nullptr;   // dense seed [N,16], zero outside the effector rows
 };
 
@@ -2397,6 +2783,7 @@ void free_effectors(hs_effectors *e)
     (void)hipFree(e->d_ids);
     (void)hipFree(e->d_row);
     (void)hipFree(e->d_tile);
+    (void)hipFree(e->d_ptile);
     (void)hipFree(e->d_dense);
     delete e;
 }
@@ -2445,23 +2832,28 @@ hs_status hs_effectors_create(const hs_plan *plan, int64_t num_effectors, const 
             row[i] = order[i];
         }
         // each adjoint tile's range [lo, hi) of the sorted ids
-        std::vector<int32_t> tile(2 * plan->h_btiles.size(), 0);
-        int64_t covered = 0;
-        for (size_t t = 0; t < plan->h_btiles.size(); ++t) {
-            const hs::TileDesc &td = plan->h_btiles[t];
-            const auto lo = std::lower_bound(sorted.begin(), sorted.begin() + E, td.begin);
-            const auto hi = std::lower_bound(sorted.begin(), sorted.begin() + E, td.begin + td.count);
-            tile[2 * t] = (int32_t)(lo - sorted.begin());
-            tile[2 * t + 1] = (int32_t)(hi - sorted.begin());
-            covered += hi - lo;
-        }
+        auto ranges = [&](const auto &tiles, std::vector<int32_t> &tile) {
+            tile.assign(2 * tiles.size(), 0);
+            int64_t covered = 0;
+            for (size_t t = 0; t < tiles.size(); ++t) {
+                const auto lo = std::lower_bound(sorted.begin(), sorted.begin() + E, tiles[t].begin);
+                const auto hi = std::lower_bound(sorted.begin(), sorted.begin() + E, tiles[t].begin + tiles[t].count);
+                tile[2 * t] = (int32_t)(lo - sorted.begin());
+                tile[2 * t + 1] = (int32_t)(hi - sorted.begin());
+                covered += hi - lo;
+            }
+            return covered;
+        };
+        std::vector<int32_t> tile, ptile;
+        int64_t covered = ranges(plan->h_btiles, tile);
+        if (!plan->paths.h_tiles.empty()) covered = std::min(covered, ranges(plan->paths.h_tiles, ptile));
         if (covered != E) {  // the adjoint's tiles cover every joint of such a plan
             free_effectors(e);
             return fail(HS_ERR_DEVICE, "hs_effectors_create: %lld ids outside the adjoint's tiles",
                         (long long)(E - covered));
         }
         if ((err = upload(&e->d_ids, sorted)) != hipSuccess || (err = upload(&e->d_row, row)) != hipSuccess ||
-            (err = upload(&e->d_tile, tile)) != hipSuccess) {
+            (err = upload(&e->d_tile, tile)) != hipSuccess || (err = upload(&e->d_ptile, ptile)) != hipSuccess) {
             free_effectors(e);
             return fail_hip(err, "hs_effectors_create (upload)");
         }
@@ -2528,7 +2920,7 @@ hs_status hs_effector_backward(const hs_plan *plan, const hs_effectors *effector
         if (err != hipSuccess) return fail_hip(err, "hs_effector_backward (seed)");
         ba.grad_global = effectors->d_dense;
     }
-    return run_backward(plan, pa, ba, stream, "hs_effector_backward");
+    return run_backward(plan, pa, ba, stream, "hs_effector_backward", false, effectors->d_ptile);
 }
 
 hs_status hs_effector_step(const hs_plan *plan, const hs_effectors *effectors, const hs_pose_src *src,
@@ -2573,7 +2965,7 @@ hs_status hs_effector_step(const hs_plan *plan, const hs_effectors *effectors, c
     ba.eff_target = targets;
     ba.eff_forward = 1;
     ba.eff_global_out = global_out;
-    return run_backward(plan, pa, ba, stream, "hs_effector_step");
+    return run_backward(plan, pa, ba, stream, "hs_effector_step", false, effectors->d_ptile);
 }
 
 } // extern "C"

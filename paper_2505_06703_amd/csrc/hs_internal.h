@@ -165,6 +165,60 @@ struct TileLaunch {
     int32_t blocks_per_wave;  // the two-level adjoint: 64-joint blocks per wave (1 or 2)
 };
 
+// The path adjoint (hs_kernels.hip, bwd_path_kernel): every character's tree
+// cut into pieces of at most kPathLen joints, each a run down one path
+// (every joint the parent of the next), one piece per thread ("lane").  A
+// tile holds whole characters of consecutive ids; its lanes are sorted by
+// length, longest first, so that a wave's lanes walk the same number of
+// steps.  Joint k of lane l has row start[k] + l of the tile's LDS array.  The
+// tables of tiles with the same characters are the same entries.
+constexpr int kPathLen = 4;
+constexpr int kPathMaxLanes = 512;   // lanes of one tile (threads of a workgroup)
+constexpr int kPathMaxFanIn = 64;    // most lanes below one joint (each is summed by one thread)
+struct PathTile {
+    int64_t begin;      // global id of the tile's first joint
+    int32_t count;      // joints
+    int32_t lanes;      // pieces
+    int32_t lane_begin; // first entry of the lane table
+    int32_t step_begin; // first word of the step table (rounds x lanes words)
+    int32_t rounds;     // ceil(log2(lanes on the longest chain of lanes))
+    int32_t rows;       // rows of the tile's LDS array (start[] is padded)
+    int32_t start[kPathLen];
+    int32_t slot_begin; // first entry of the slot table
+    int32_t pad[3];
+};
+static_assert(sizeof(PathTile) == 64, "PathTile layout");
+
+// One lane.  A joint below which other lanes hang is a branch; the tile's
+// branches are numbered lane by lane, in joint order.
+struct PathLane {
+    int32_t up;    // (1 + lane of the head's parent, 0: the head is a root) | joints << 16
+    int32_t down;  // bit k: joint k is a branch | number of the lane's first branch << 8
+    int32_t from;  // 1 + branch of the head's parent, 0: the head is a root
+    uint32_t kids; // byte k: lanes directly below joint k
+};
+static_assert(sizeof(PathLane) == 16 && kPathLen <= 4, "PathLane layout");
+
+// One round of jumping over the lanes, as one lane sees it: the row that it
+// leaves its contribution in, and the rows that it adds (the first one, and
+// how many).  A round's rows are sorted by receiver, in the first round by
+// branch, so that the lanes below one joint lie together.
+constexpr uint32_t path_step(uint32_t row, uint32_t first, uint32_t count) { return row | first << 10 | count << 20; }
+constexpr int path_step_row(uint32_t s) { return (int)(s & 1023); }
+constexpr int path_step_first(uint32_t s) { return (int)(s >> 10 & 1023); }
+constexpr int path_step_count(uint32_t s) { return (int)(s >> 20); }
+
+struct PathLaunch {
+    const PathTile *tiles;    // heaviest first
+    int32_t num_tiles;
+    int32_t threads;          // of a workgroup: at least every tile's lanes, a multiple of 64
+    int32_t max_lanes, max_rows, max_count;  // of one tile
+    const PathLane *lanes;
+    const uint32_t *steps;
+    const uint16_t *slot;     // each joint's row in its tile
+    const uint32_t *gate;     // as TileLaunch::gate
+};
+
 // The one-pass path for chain characters on the multipass path (every
 // joint's parent the previous joint): 64-joint blocks in chain order,
 // grouped into superblocks of up to 64 consecutive blocks of one chain.
@@ -257,6 +311,7 @@ hipError_t launch_forward_tiles(const TileLaunch &tl, const PoseArgs &pose, cons
 hipError_t launch_forward_queue(const QueueLaunch &ql, const PoseArgs &pose, const OutArgs &out,
                                 hipStream_t stream);
 size_t forward_queue_lds_bytes(int waves, int max_anchors, int tile_cap, bool sample, bool skin);
+size_t backward_path_lds_bytes(int max_lanes, int max_rows, int max_count, bool effectors);
 size_t backward_anchor_lds_bytes(int waves, int max_anchors, int tile_cap);
 // Workgroups of the two-level adjoint (waves per workgroup, blocks per
 // wave, seed kind 0 dense / 1 effectors / 2 forward in the tile) that fit
@@ -276,6 +331,7 @@ constexpr int kChainWaves = 16;     // waves per workgroup of the chain kernel
 constexpr int kChainSBBlocks = 64;  // 64-joint blocks per superblock of the chain kernel
 hipError_t launch_backward_tiles(const TileLaunch &tl, const PoseArgs &pose, const BwdArgs &bwd,
                                  hipStream_t stream);
+hipError_t launch_backward_paths(const PathLaunch &pl, const PoseArgs &pose, const BwdArgs &bwd, hipStream_t stream);
 hipError_t launch_backward_multipass(const MPLaunch &ml, const PoseArgs &pose, const BwdArgs &bwd,
                                      hipStream_t stream);
 hipError_t launch_pose_sample(const TileLaunch &tl, const MPLaunch &ml, const ChainLaunch &cl, const PoseArgs &pose,

@@ -1215,6 +1215,20 @@ __device__ __forceinline__ void adj_pull(const float X[12], const float L[12], f
     }
 }
 
+// acc += X (.) L
+__device__ __forceinline__ void adj_pull_add(const float X[12], const float L[12], float acc[12])
+{
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const float x0 = X[4 * r], x1 = X[4 * r + 1], x2 = X[4 * r + 2], x3 = X[4 * r + 3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            acc[4 * r + c] = fmaf(x0, L[4 * c], fmaf(x1, L[4 * c + 1],
+                                                     fmaf(x2, L[4 * c + 2], fmaf(x3, L[4 * c + 3], acc[4 * r + c]))));
+        acc[4 * r + 3] += x3;
+    }
+}
+
 __device__ __forceinline__ void lds_atomic_add12(float4 *dst, const float v[12])
 {
     float *d = reinterpret_cast<float *>(dst);
@@ -1222,19 +1236,11 @@ __device__ __forceinline__ void lds_atomic_add12(float4 *dst, const float v[12])
     for (int k = 0; k < 12; ++k) atomicAdd(d + k, v[k]);
 }
 
-// Gradients of joint gid from its total adjoint X and the parent's global
-// rotation-scale block Ap (row-major 3x3).
-__device__ __forceinline__ void write_grads(const BwdArgs &B, int64_t gid, const float X[12], const float Ap[9],
-                                            float4 q, float sx, float sy, float sz)
+// Gradients of joint gid from dLoss/dL = [Rb | tb], the adjoint of its local
+// transform (Rb row-major 3x3).
+__device__ __forceinline__ void write_local_grads(const BwdArgs &B, int64_t gid, const float Rb[9], const float tb[3],
+                                                  float4 q, float sx, float sy, float sz)
 {
-    float Rb[9], tb[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-#pragma unroll
-        for (int l = 0; l < 3; ++l)
-            Rb[3 * i + l] = fmaf(Ap[i], X[l], fmaf(Ap[3 + i], X[4 + l], Ap[6 + i] * X[8 + l]));
-        tb[i] = fmaf(Ap[i], X[3], fmaf(Ap[3 + i], X[7], Ap[6 + i] * X[11]));
-    }
     const float x = q.x, y = q.y, z = q.z, w = q.w;
     const float sc[3] = {sx, sy, sz};
     if (B.grad_scale) {
@@ -1260,6 +1266,22 @@ __device__ __forceinline__ void write_grads(const BwdArgs &B, int64_t gid, const
     gt[0] = tb[0];
     gt[1] = tb[1];
     gt[2] = tb[2];
+}
+
+// Gradients of joint gid from its total adjoint X and the parent's global
+// rotation-scale block Ap (row-major 3x3).
+__device__ __forceinline__ void write_grads(const BwdArgs &B, int64_t gid, const float X[12], const float Ap[9],
+                                            float4 q, float sx, float sy, float sz)
+{
+    float Rb[9], tb[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int l = 0; l < 3; ++l)
+            Rb[3 * i + l] = fmaf(Ap[i], X[l], fmaf(Ap[3 + i], X[4 + l], Ap[6 + i] * X[8 + l]));
+        tb[i] = fmaf(Ap[i], X[3], fmaf(Ap[3 + i], X[7], Ap[6 + i] * X[11]));
+    }
+    write_local_grads(B, gid, Rb, tb, q, sx, sy, sz);
 }
 
 // LDS: G[cap][3] | adjoint accumulators[cap][3] float4 | owner words[cap] uint16 |
@@ -2097,6 +2119,414 @@ const void *anchor_kernel_of(int seed)
     if (seed == kSeedForward) return reinterpret_cast<const void *>(bwd_anchor_kernel<W, BPW, kSeedForward>);
     if (seed == kSeedEffectors) return reinterpret_cast<const void *>(bwd_anchor_kernel<W, BPW, kSeedEffectors>);
     return reinterpret_cast<const void *>(bwd_anchor_kernel<W, BPW, kSeedDense>);
+}
+
+// ---------------------------------------------------------------------------
+// Path adjoint (tiles of whole characters of up to 1024 joints).
+//
+// Pointer jumping spends log2(depth) compositions per joint, forward and
+// again reverse.  Here a thread walks a piece of a path -- up to kPathLen
+// joints, each the parent of the next, its "lane" -- one composition a joint,
+// and only the lanes' totals are jumped over, a few hundred of them a tile.
+// With Q_k the product of a lane's local transforms down to its joint k,
+// W = sum_k D_k (.) Q_k is what the lane's own seeds send to the joint above
+// its head, M = Q of that joint in its lane is the lane's step up the tree of
+// lanes, and
+//     W_total(l) = W(l) + sum over the lanes c below l of W_total(c) (.) M(c),
+//     T(l)       = T(lane above) M(l)     (T: G of the joint above the head)
+// are the adjoint and the scan again on that smaller tree.  Then one walk up
+// each lane adds what hangs below each joint (X_k = D_k + sum of W_total of
+// the lanes below joint k + X_{k+1} (.) L_{k+1}), and one walk down carries G
+// and turns X_k into dLoss/dL_k = A_{k-1}^T X_k.
+//
+// What bounds it: the latency of one tile's phases (45 thousand clocks, of
+// which a wave issues for 8), with the arithmetic of the walks (five
+// compositions a joint) and HBM behind it.  Four joints a lane keep the local
+// transforms and adjoints of a lane in 166 registers, three waves a SIMD; with
+// eight (two waves) 2048 characters of 32 to 1024 joints took 75 us instead of
+// 62, 1024 x 512 joints 27.0 instead of 25.4.  The one LDS array, 48 bytes a
+// joint, turns joint order (coalesced loads and stores) into lanes and back,
+// and holds the lanes' arrays in between.  Senders' rows planned ahead instead
+// of lists built with LDS exchanges (dozens of lanes reach one lane on bushy
+// trees, a round trip each): 62 -> 54 us there.  Against the synchronous
+// rounds: 2048 x 32..1024 joints 118 -> 54 us, 10 000 x 256 joints 170 -> 92 us
+// (its 307 MB need 60 us at the rate of a copy); against the two-level kernel,
+// end-effector steps of 1024 x 512 joints 33.7 -> 25.8 us.
+//
+// LDS: rows [max_rows][3] f4, or in their place Mx [lanes][3] f4 (first the
+// branches' products), Cx [lanes][3] f4 and ax [lanes] int | slots [max_count]
+// uint16 | (effector seeds) effk [max_rows] uint16
+// ---------------------------------------------------------------------------
+__host__ __device__ inline size_t path_shared_bytes(int max_lanes, int max_rows)
+{
+    const size_t r = (size_t)max_rows * 48, l = (size_t)max_lanes * (2 * 48 + 4);
+    return ((r > l ? r : l) + 15) / 16 * 16;
+}
+
+// Row i of an LDS array of three float4 (a 24-bit product: the compiler's own
+// index arithmetic is 64 bits wide here).
+__device__ __forceinline__ float4 *row_at(float4 *p, int i)
+{
+    return p + __umul24((unsigned)i, 3u);
+}
+
+template <int WAVES>
+__device__ __forceinline__ void path_sync()
+{
+    if constexpr (WAVES == 1) wave_sync();
+    else __syncthreads();
+}
+
+// Pointer jumping over the tile's lanes, one per thread (a: the lane above,
+// or -1): M becomes the product down the whole chain of lanes, and with REV
+// S the sum over the lanes below.  Who sends to whom in a round is the plan's:
+// the senders to a lane leave their contributions in consecutive rows (steps:
+// one word per round and lane), so that their sum has one order and no list
+// is built or followed.  SPARSE: lanes with no seed below them send zeros.
+template <int WAVES, bool REV, bool SPARSE>
+__device__ __forceinline__ void path_rounds(float M[12], float S[12], int a, int rounds, int tid, bool lane, int nl,
+                                            uint32_t step, const uint32_t *steps, float4 *Mx, float4 *Cx, int *ax)
+{
+#pragma unroll 1
+    for (int r = 0; r < rounds; ++r) {  // a uniform count: every wave meets every barrier
+        const bool act = a >= 0;
+        uint32_t next = 0;  // the next round's word, loaded a round ahead
+        if constexpr (REV) {
+            if (lane && r + 1 < rounds) next = steps[(r + 1) * nl + tid];
+        }
+        path_sync<WAVES>();  // the previous round's reads are done
+        if (lane) {
+            aff_store(row_at(Mx, tid), M);
+            ax[tid] = a;
+        }
+        if constexpr (REV) {
+            if (act) {
+                float c[12];
+                adj_pull(S, M, c);
+                if constexpr (SPARSE) {
+                    if (!any_nonzero12(S)) {
+#pragma unroll
+                        for (int k = 0; k < 12; ++k) c[k] = 0.0f;
+                    }
+                }
+                aff_store(row_at(Cx, path_step_row(step)), c);
+            }
+        }
+        path_sync<WAVES>();
+        if constexpr (REV) {
+            int i = path_step_first(step);
+            const int e = i + path_step_count(step);
+            for (; i + 1 < e; i += 2) {
+                float c0[12], c1[12];
+                aff_load(row_at(Cx, i), c0);
+                aff_load(row_at(Cx, i + 1), c1);
+#pragma unroll
+                for (int k = 0; k < 12; ++k) S[k] += c0[k] + c1[k];
+            }
+            if (i < e) {
+                float c[12];
+                aff_load(row_at(Cx, i), c);
+#pragma unroll
+                for (int k = 0; k < 12; ++k) S[k] += c[k];
+            }
+        }
+        if (act) {
+            float ma[12];
+            aff_load(row_at(Mx, a), ma);
+            a = ax[a];
+            aff_mul_left(ma, M);
+        }
+        step = next;
+    }
+}
+
+template <int WAVES, int SEED>
+__global__ void __launch_bounds__(WAVES * kWave, 3)  // at most 168 VGPRs: three waves per SIMD
+bwd_path_kernel(PathLaunch pl, PoseArgs pose, BwdArgs bwd)
+{
+    constexpr int K = kPathLen;
+    extern __shared__ float4 lds[];
+    if (gated(pl.gate)) return;
+    const int T = (int)blockDim.x;
+    const int tid = threadIdx.x;
+    const PathTile td = pl.tiles[blockIdx.x];
+    const int n = td.count;
+    const int64_t begin = td.begin;
+    const int nl = td.lanes;
+    float4 *rows = lds;
+    float4 *Mx = lds;  // the lanes' arrays, while the rows hold nothing
+    float4 *Cx = row_at(Mx, nl);
+    int *ax = reinterpret_cast<int *>(row_at(Cx, nl));
+    const uint32_t *steps = pl.steps + td.step_begin;
+    uint16_t *slots = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds) +
+                                                   path_shared_bytes(pl.max_lanes, pl.max_rows));
+    uint16_t *effk = slots + pl.max_count;  // 1 + the seed of each row, counted in the tile
+
+    // the lane (threads past the tile's lanes hold an empty one)
+    PathLane ld{0, 0, 0, 0};
+    uint32_t step0 = 0;  // the first round's word
+    if (tid < nl) {
+        ld = pl.lanes[td.lane_begin + tid];
+        if (td.rounds > 0) step0 = pl.steps[td.step_begin + tid];
+    }
+    const int len = ld.up >> 16;
+    const int above = (ld.up & 0xffff) - 1;
+    const int mask = ld.down & 0xff;
+    const int b0 = ld.down >> 8;
+    const int from = ld.from - 1;
+    const uint32_t kids = ld.kids;
+    const int wlen = __builtin_amdgcn_readfirstlane(len);  // the wave's longest lane comes first
+
+    int e0 = 0, e1 = 0;  // the tile's seeds
+    if constexpr (SEED != kSeedDense) {
+        e0 = bwd.eff_tile[2 * blockIdx.x];
+        e1 = bwd.eff_tile[2 * blockIdx.x + 1];
+    }
+
+    // joint order -> rows -> the lanes' registers: seeds, then local transforms
+    float L[K][12], X[K][12];
+    {
+        float4 q[K];
+        float t[K][3], s[K][3];
+        int sl[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (i * T >= n) break;
+            const int jl = min(tid + i * T, n - 1);  // past the tile: its last joint, not used
+            sl[i] = pl.slot[td.slot_begin + jl];
+            load_trs(pose, begin + jl, q[i], t[i], s[i]);
+        }
+        if constexpr (SEED == kSeedDense) {
+            native_float4 d[K][3];
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                if (i * T >= n) break;
+                const native_float4 *gg =
+                    reinterpret_cast<const native_float4 *>(bwd.grad_global) + 4 * (begin + min(tid + i * T, n - 1));
+#pragma unroll
+                for (int r = 0; r < 3; ++r) d[i][r] = gg[r];
+            }
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                if (i * T >= n) break;
+                if (tid + i * T < n) {
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) reinterpret_cast<native_float4 *>(rows)[3 * sl[i] + r] = d[i][r];
+                }
+            }
+            path_sync<WAVES>();
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) X[k][c] = 0.0f;
+                if (k < len) aff_load(row_at(rows, (td.start[k] + tid)), X[k]);
+            }
+            path_sync<WAVES>();
+        } else {
+            for (int i = tid; i < td.rows; i += T) effk[i] = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            if (i * T >= n) break;
+            if (tid + i * T < n) {
+                float m[12];
+                aff_from_trs(q[i], t[i][0], t[i][1], t[i][2], s[i][0], s[i][1], s[i][2], m);
+                aff_store(row_at(rows, sl[i]), m);
+                slots[tid + i * T] = (uint16_t)sl[i];
+            }
+        }
+        path_sync<WAVES>();
+    }
+    if constexpr (SEED != kSeedDense) {
+        for (int k = tid; e0 + k < e1; k += T) effk[slots[(int)(bwd.eff_ids[e0 + k] - begin)]] = (uint16_t)(k + 1);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        aff_identity(L[k]);
+        if (k < len) aff_load(row_at(rows, (td.start[k] + tid)), L[k]);
+        if constexpr (SEED != kSeedDense) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) X[k][c] = 0.0f;
+        }
+    }
+    path_sync<WAVES>();  // the rows are in registers: the lanes' arrays take their place
+
+    // walk down: Q, the branches' products, and (seeds known) W
+    float M[12], W[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) W[c] = 0.0f;
+    float tq[SEED == kSeedForward ? K : 1][3];  // Q's translations: W of seeds known only after the scan
+    {
+        float Q[12];
+        int bi = b0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (k >= wlen) continue;
+            if (k == 0) {
+#pragma unroll
+                for (int c = 0; c < 12; ++c) Q[c] = L[0][c];
+            } else {
+                float o[12];
+                aff_mul(Q, L[k], o);
+#pragma unroll
+                for (int c = 0; c < 12; ++c) Q[c] = o[c];
+            }
+            if (mask >> k & 1) aff_store(row_at(Mx, bi++), Q);
+            if constexpr (SEED == kSeedForward) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r) tq[k][r] = Q[4 * r + 3];
+            } else {
+                bool any = k < len;
+                if constexpr (SEED == kSeedEffectors) {
+                    int e = k < len ? effk[td.start[k] + tid] : 0;
+                    any = e > 0;
+                    if (any) {
+                        e += e0 - 1;
+                        const float *y = bwd.eff_target + 3 * (int64_t)bwd.eff_row[e];
+                        const float *g = bwd.eff_global + 16 * bwd.eff_ids[e];
+#pragma unroll
+                        for (int r = 0; r < 3; ++r) X[k][4 * r + 3] = 2.0f * (g[4 * r + 3] - y[r]);
+                    }
+                }
+                if (any) adj_pull_add(X[k], Q, W);
+            }
+        }
+    }
+    path_sync<WAVES>();
+    if (from >= 0) aff_load(row_at(Mx, from), M);
+    else aff_identity(M);
+
+    constexpr bool SPARSE = SEED != kSeedDense;
+    float G[12];  // T: G of the joint above the lane's head
+    if constexpr (SEED == kSeedForward) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) G[c] = M[c];
+        path_rounds<WAVES, false, false>(G, W, above, td.rounds, tid, tid < nl, nl, step0, steps, Mx, Cx, ax);
+        path_sync<WAVES>();  // rows again, for G
+        float g[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) g[c] = G[c];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (k >= wlen) continue;
+            float o[12];
+            aff_mul(g, L[k], o);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) g[c] = o[c];
+            if (k < len) {
+                const int row = td.start[k] + tid;
+                if (bwd.eff_global_out) aff_store(row_at(rows, row), g);
+                int e = effk[row];
+                if (e > 0) {
+                    e += e0 - 1;
+                    const float *y = bwd.eff_target + 3 * (int64_t)bwd.eff_row[e];
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) {
+                        const float b = 2.0f * (g[4 * r + 3] - y[r]);
+                        X[k][4 * r + 3] = b;
+                        // [0 | b] (.) [R | t] = [b t^T | b]
+                        W[4 * r] = fmaf(b, tq[k][0], W[4 * r]);
+                        W[4 * r + 1] = fmaf(b, tq[k][1], W[4 * r + 1]);
+                        W[4 * r + 2] = fmaf(b, tq[k][2], W[4 * r + 2]);
+                        W[4 * r + 3] += b;
+                    }
+                }
+            }
+        }
+        if (bwd.eff_global_out) {
+            path_sync<WAVES>();
+            float4 *dst = reinterpret_cast<float4 *>(bwd.eff_global_out) + 4 * begin;
+#pragma unroll 4
+            for (int c = tid; c < 4 * n; c += T) {
+                const int r = c & 3;
+                const float4 v = rows[3 * slots[c >> 2] + (r == 3 ? 0 : r)];
+                store_stream(dst + c, r == 3 ? make_float4(0.0f, 0.0f, 0.0f, 1.0f) : v);
+            }
+        }
+    }
+    path_rounds<WAVES, true, SPARSE>(M, W, above, td.rounds, tid, tid < nl, nl, step0, steps, Mx, Cx, ax);
+    if constexpr (SEED != kSeedForward) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) G[c] = M[c];
+    }
+
+    // what each lane sends to the joint above its head, in the first round's
+    // rows (a joint's lanes lie together there)
+    path_sync<WAVES>();
+    if (above >= 0) aff_store(row_at(Cx, path_step_row(step0)), W);
+    path_sync<WAVES>();
+
+    // walk up: X_k, what hangs below joint k included
+    {
+        int i = path_step_first(step0) + path_step_count(step0);
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            if (k < wlen) {
+                for (int e = i - (kids >> 8 * k & 0xff); i > e;) {
+                    float in[12];
+                    aff_load(row_at(Cx, --i), in);
+#pragma unroll
+                    for (int c = 0; c < 12; ++c) X[k][c] += in[c];
+                }
+                if (k > 0) adj_pull_add(X[k], L[k], X[k > 0 ? k - 1 : 0]);
+            }
+        }
+    }
+
+    path_sync<WAVES>();  // the lanes' arrays have been read: rows again
+
+    // walk down: dLoss/dL_k = (parent's rotation-scale block)^T X_k
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (k >= wlen) continue;
+        if (k < len) {
+            float z[12];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    z[4 * i + c] = fmaf(G[i], X[k][c], fmaf(G[4 + i], X[k][4 + c], G[8 + i] * X[k][8 + c]));
+            aff_store(row_at(rows, (td.start[k] + tid)), z);
+        }
+        float o[12];
+        aff_mul(G, L[k], o);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) G[c] = o[c];
+    }
+
+    // rows -> joint order; the pose is read again (from the caches), which
+    // the compiler must not turn into keeping it, or its addresses, in
+    // registers all along
+    int j0 = tid;
+    asm volatile("" : "+s"(pose.quat), "+s"(pose.scale), "+v"(j0));
+    float4 q[K];
+    float t[3], s[K][3];
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        if (i * T >= n) break;
+        load_trs(pose, begin + min(j0 + i * T, n - 1), q[i], t, s[i]);
+    }
+    path_sync<WAVES>();
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        if (i * T >= n) break;
+        const int jl = j0 + i * T;
+        if (jl < n) {
+            float z[12];
+            aff_load(row_at(rows, slots[jl]), z);
+            const float Rb[9] = {z[0], z[1], z[2], z[4], z[5], z[6], z[8], z[9], z[10]};
+            const float tb[3] = {z[3], z[7], z[11]};
+            write_local_grads(bwd, begin + jl, Rb, tb, q[i], s[i][0], s[i][1], s[i][2]);
+        }
+    }
+}
+
+template <int WAVES>
+const void *path_kernel_of(int seed)
+{
+    if (seed == kSeedForward) return reinterpret_cast<const void *>(bwd_path_kernel<WAVES, kSeedForward>);
+    if (seed == kSeedEffectors) return reinterpret_cast<const void *>(bwd_path_kernel<WAVES, kSeedEffectors>);
+    return reinterpret_cast<const void *>(bwd_path_kernel<WAVES, kSeedDense>);
 }
 
 // ---------------------------------------------------------------------------
@@ -3744,6 +4174,17 @@ hipError_t prepare_kernels()
         (err = hipFuncSetAttribute(reinterpret_cast<const void *>(mp_chain_kernel<true>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainLdsBytes)) != hipSuccess)
         return err;
+    {
+        int dev = 0, lds_max = 0;
+        if ((err = hipGetDevice(&dev)) != hipSuccess) return err;
+        if ((err = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)) != hipSuccess)
+            return err;
+        for (int seed = 0; seed < 3; ++seed)
+            for (const void *k : {path_kernel_of<1>(seed), path_kernel_of<2>(seed), path_kernel_of<4>(seed),
+                                  path_kernel_of<8>(seed)})
+                if ((err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max)) != hipSuccess)
+                    return err;
+    }
     if ((err = set_lds_limits<1>()) != hipSuccess) return err;
     if ((err = set_lds_limits<2>()) != hipSuccess) return err;
     if ((err = set_lds_limits<4>()) != hipSuccess) return err;
@@ -4150,6 +4591,11 @@ size_t backward_anchor_lds_bytes(int waves, int max_anchors, int tile_cap)
     return (size_t)waves * kWave * (2 * 48 + 3 * 4) + (size_t)max_anchors * (3 * 48 + 12) + (size_t)tile_cap * 4;
 }
 
+size_t backward_path_lds_bytes(int max_lanes, int max_rows, int max_count, bool effectors)
+{
+    return path_shared_bytes(max_lanes, max_rows) + (size_t)max_count * 2 + (effectors ? (size_t)max_rows * 2 : 0);
+}
+
 size_t backward_sync_lds_bytes(int tile_cap)
 {
     return (size_t)tile_cap * 104 + (size_t)(tile_cap / kWave + 1) * 4;
@@ -4282,6 +4728,33 @@ hipError_t launch_backward_tiles(const TileLaunch &tl, const PoseArgs &pose, con
     case 16: return launch_bwd_sync_w<16>(t2, pose, bwd, stream);
     default: return hipErrorInvalidValue;
     }
+}
+
+template <int WAVES>
+hipError_t launch_bwd_path_t(const PathLaunch &pl, const PoseArgs &pose, const BwdArgs &bwd, hipStream_t stream)
+{
+    const dim3 grid(pl.num_tiles), blk(pl.threads);
+    const size_t lds = backward_path_lds_bytes(pl.max_lanes, pl.max_rows, pl.max_count, bwd.eff_ids != nullptr);
+    if (bwd.eff_ids && bwd.eff_forward)
+        hipLaunchKernelGGL((bwd_path_kernel<WAVES, kSeedForward>), grid, blk, lds, stream, pl, pose, bwd);
+    else if (bwd.eff_ids)
+        hipLaunchKernelGGL((bwd_path_kernel<WAVES, kSeedEffectors>), grid, blk, lds, stream, pl, pose, bwd);
+    else
+        hipLaunchKernelGGL((bwd_path_kernel<WAVES, kSeedDense>), grid, blk, lds, stream, pl, pose, bwd);
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_paths(const PathLaunch &pl, const PoseArgs &pose, const BwdArgs &bwd, hipStream_t stream)
+{
+    if (pl.num_tiles == 0) return hipSuccess;
+    // a thread per lane, and kPathLen joints a thread in joint order
+    if (pl.threads < kWave || pl.threads % kWave != 0 || pl.threads > kPathMaxLanes ||
+        pl.max_lanes > pl.threads || pl.max_count > pl.threads * kPathLen)
+        return hipErrorInvalidValue;
+    if (pl.threads <= kWave) return launch_bwd_path_t<1>(pl, pose, bwd, stream);
+    if (pl.threads <= 2 * kWave) return launch_bwd_path_t<2>(pl, pose, bwd, stream);
+    if (pl.threads <= 4 * kWave) return launch_bwd_path_t<4>(pl, pose, bwd, stream);
+    return launch_bwd_path_t<8>(pl, pose, bwd, stream);
 }
 
 hipError_t launch_backward_multipass(const MPLaunch &ml, const PoseArgs &pose, const BwdArgs &bwd,
