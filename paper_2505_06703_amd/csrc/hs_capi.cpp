@@ -2029,8 +2029,9 @@ hs_status create_plan(hs_context *ctx, const hs_batch *batch, const hs_plan_opts
         }
     }
     if (off[C] != N) {
+        const long long end = off[C];  // off is the plan's
         free_plan(plan);
-        return fail(HS_ERR_INVALID_ARG, "joint_offsets[C] = %lld but num_joints = %lld", (long long)off[C], (long long)N);
+        return fail(HS_ERR_INVALID_ARG, "joint_offsets[C] = %lld but num_joints = %lld", end, (long long)N);
     }
     plan->h_gparent = gparent;
     plan->h_level = level;
