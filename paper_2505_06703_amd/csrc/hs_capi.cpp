@@ -86,6 +86,45 @@ hipError_t upload(T **dst, const std::vector<T> &src)
     return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
 }
 
+// Several tables or workspaces in one allocation, each 256-byte aligned: an
+// allocation costs a plan more than most tables' copies do.  add() and room()
+// return offsets for at(); what was added is copied by upload().
+struct Block {
+    struct Table {
+        const void *src;
+        size_t offset, bytes;
+    };
+    std::vector<Table> tables;
+    size_t size = 0;
+    template <class T>
+    size_t add(const std::vector<T> &src)
+    {
+        const size_t at = room(src.size() * sizeof(T));
+        if (!src.empty()) tables.push_back({src.data(), at, src.size() * sizeof(T)});
+        return at;
+    }
+    size_t room(size_t n)
+    {
+        const size_t at = size;
+        size = (size + n + 255) / 256 * 256;
+        return at;
+    }
+    hipError_t upload(char **dst) const
+    {
+        *dst = nullptr;
+        if (size == 0) return hipSuccess;
+        hipError_t err = hipMalloc(reinterpret_cast<void **>(dst), size);
+        for (const Table &t : tables)
+            if (err == hipSuccess) err = hipMemcpy(*dst + t.offset, t.src, t.bytes, hipMemcpyHostToDevice);
+        return err;
+    }
+};
+template <class T>
+T *at(char *base, size_t offset)
+{
+    return reinterpret_cast<T *>(base + offset);
+}
+
 // Copy n elements from a host or device pointer into a host vector.
 template <class T>
 hipError_t fetch(std::vector<T> &dst, const T *src, size_t n)
@@ -111,7 +150,7 @@ hipError_t fetch(std::vector<T> &dst, const T *src, size_t n)
 template <class F>
 void parallel_pieces(int64_t n, int64_t work, F f)
 {
-    const int64_t most = std::min<int64_t>({8, (int64_t)std::thread::hardware_concurrency(), work >> 16, n});
+    const int64_t most = std::min<int64_t>({8, (int64_t)std::thread::hardware_concurrency(), work >> 18, n});
     if (most < 2) {
         if (n > 0) f((int64_t)0, n);
         return;
@@ -379,6 +418,7 @@ hs_status save_tuning_file(const hs_context *ctx, const char *path)
 
 // Device tables and workspace of the multipass path.
 struct MPSet {
+    char *d_mem = nullptr;       // the allocation of everything but the chain path's
     MPBlock *d_blocks = nullptr;
     int32_t num_blocks = 0;
     int64_t nmp = 0;
@@ -386,15 +426,21 @@ struct MPSet {
     int32_t *d_aself = nullptr;  // each joint's own anchor index, or -1
     int32_t *d_aseg = nullptr;   // in-LDS segments of the anchor rounds (offsets)
     int32_t num_aseg = 0;
+    hs::MPTree *d_trees = nullptr;  // the anchors level by level instead of in rounds
+    int32_t num_trees = 0, tree_anchors = 0;
+    int32_t *d_lev = nullptr;
+    int2 *d_kids = nullptr;
     int32_t num_anchors = 0;
     int32_t rounds = 0;        // anchor-level jump rounds
     float4 *A1 = nullptr;      // anchors' phase-1 products
     int32_t *E1 = nullptr;
     float4 *AP[2] = {nullptr, nullptr};
     int32_t *AE[2] = {nullptr, nullptr};
-    // adjoint: anchor adjoints, compact G
+    // adjoint: anchor adjoints, the heads' rows and their tables
     float4 *S[2] = {nullptr, nullptr};
-    float4 *G = nullptr;
+    float4 *H = nullptr;
+    int32_t *d_hanc = nullptr;
+    int32_t *d_hfirst = nullptr;
     // the one-pass chain path (forward set only): chain characters' blocks
     // and superblocks, their workspace, and the resident grid per pose kind
     hs::ChainBlock *d_cblocks = nullptr;
@@ -409,18 +455,7 @@ struct MPSet {
 
 void free_mpset(MPSet &m)
 {
-    (void)hipFree(m.d_blocks);
-    (void)hipFree(m.d_janc);
-    (void)hipFree(m.d_aself);
-    (void)hipFree(m.d_aseg);
-    (void)hipFree(m.A1);
-    (void)hipFree(m.E1);
-    for (int i = 0; i < 2; ++i) {
-        (void)hipFree(m.AP[i]);
-        (void)hipFree(m.AE[i]);
-        (void)hipFree(m.S[i]);
-    }
-    (void)hipFree(m.G);
+    (void)hipFree(m.d_mem);
     (void)hipFree(m.d_cblocks);
     (void)hipFree(m.d_csb);
     (void)hipFree(m.c_recs);
@@ -437,6 +472,7 @@ struct hs_plan {
     hs_plan_info info{};
     Shape shape;
     // device tables
+    char *d_base = nullptr;      // the allocation of the next three and the status word
     int64_t *d_offsets = nullptr;
     int32_t *d_parent = nullptr;  // global parent id or -1
     int32_t *d_level = nullptr;
@@ -452,6 +488,7 @@ struct hs_plan {
     std::vector<ClassSet> small;
     // adjoint tiles: characters of up to 1024 joints (synchronous-round
     // kernel) and larger ones up to the dataflow kernel's limit
+    char *d_adjoint = nullptr;   // the allocation of d_btiles, d_bbig and d_bcode
     TileDesc *d_btiles = nullptr;
     std::vector<TileDesc> h_btiles;
     int32_t num_btiles = 0;
@@ -514,21 +551,16 @@ void free_paths(hs_plan::PathSet &ps)
 void free_plan(hs_plan *p)
 {
     if (!p) return;
-    (void)hipFree(p->d_offsets);
-    (void)hipFree(p->d_parent);
-    (void)hipFree(p->d_level);
+    (void)hipFree(p->d_base);
     (void)hipFree(p->d_tiles);
     for (auto &c : p->small) (void)hipFree(c.d_tiles);
-    (void)hipFree(p->d_btiles);
-    (void)hipFree(p->d_bbig);
+    (void)hipFree(p->d_adjoint);
     free_mpset(p->mp);
     free_mpset(p->bmp);
     (void)hipFree(p->d_skel_parent);
     (void)hipFree(p->d_char_skel);
-    (void)hipFree(p->d_status);
     (void)hipFree(p->q.d_tiles);
     (void)hipFree(p->q.d_code);
-    (void)hipFree(p->d_bcode);
     free_paths(p->paths);
     delete p;
 }
@@ -735,26 +767,34 @@ void build_anchors(const hs_plan *plan, const Packing &pk, std::vector<int32_t> 
                    std::vector<int32_t> &anchors, int &rounds)
 {
     const auto &gpar = plan->h_gparent;
-    std::vector<int32_t> e((size_t)pk.nmp, -1);
-    for (const MPBlock &bd : pk.mpb)
-        for (int l = 0; l < bd.count; ++l) {
-            const int64_t g = bd.gbegin + l, c = bd.cbegin + l;
-            const int64_t p = gpar[g];
-            if (p < 0) e[c] = -1;
-            else if (p >= bd.gbegin) e[c] = e[bd.cbegin + (p - bd.gbegin)];
-            else e[c] = (int32_t)(bd.cbegin + (p - bd.gbegin));  // same character, earlier block
+    const int64_t nb = (int64_t)pk.mpb.size();
+    janc.resize((size_t)pk.nmp);  // first e(c); e of a joint depends on its own block alone
+    parallel_pieces(nb, pk.nmp, [&](int64_t b0, int64_t b1) {
+        for (int64_t b = b0; b < b1; ++b) {
+            const MPBlock &bd = pk.mpb[b];
+            for (int l = 0; l < bd.count; ++l) {
+                const int64_t p = gpar[bd.gbegin + l], c = bd.cbegin + l;
+                janc[c] = p < 0 ? -1 : p >= bd.gbegin ? janc[bd.cbegin + (p - bd.gbegin)]
+                                                      : (int32_t)(bd.cbegin + (p - bd.gbegin));  // same character
+            }
         }
-    std::vector<int32_t> aidx((size_t)pk.nmp, -1);
-    for (int64_t c = 0; c < pk.nmp; ++c)
-        if (e[c] >= 0) aidx[e[c]] = 0;
+    });
+    // the anchors as a bit set; an anchor's index is its rank there
+    std::vector<uint64_t> set((size_t)(pk.nmp + 63) / 64, 0);
+    for (int64_t c = 0, last = -1; c < pk.nmp; ++c)
+        if (janc[c] != last && (last = janc[c]) >= 0) set[last >> 6] |= uint64_t(1) << (last & 63);
+    std::vector<int32_t> rank(set.size());
     anchors.clear();
-    for (int64_t c = 0; c < pk.nmp; ++c)
-        if (aidx[c] == 0) {
-            aidx[c] = (int32_t)anchors.size();
-            anchors.push_back((int32_t)c);
-        }
-    janc.assign((size_t)pk.nmp, -1);
-    for (int64_t c = 0; c < pk.nmp; ++c) janc[c] = e[c] >= 0 ? aidx[e[c]] : -1;
+    for (size_t w = 0; w < set.size(); ++w) {
+        rank[w] = (int32_t)anchors.size();
+        for (uint64_t bits = set[w]; bits; bits &= bits - 1)
+            anchors.push_back((int32_t)(64 * w) + __builtin_ctzll(bits));
+    }
+    parallel_pieces(nb, pk.nmp, [&](int64_t b0, int64_t b1) {
+        for (int64_t c = pk.mpb[b0].cbegin, end = pk.mpb[b1 - 1].cbegin + pk.mpb[b1 - 1].count; c < end; ++c)
+            if (const int32_t e = janc[c]; e >= 0)
+                janc[c] = rank[e >> 6] + __builtin_popcountll(set[e >> 6] & ((uint64_t(1) << (e & 63)) - 1));
+    });
     // anchors come in joint order and e(a) < a, so a chain's depth is known
     // when its anchor is reached
     std::vector<int32_t> depth(anchors.size(), 1);
@@ -765,6 +805,68 @@ void build_anchors(const hs_plan *plan, const Packing &pk, std::vector<int32_t> 
         maxd = std::max(maxd, depth[i]);
     }
     rounds = ceil_log2(maxd);
+}
+
+// Sort each character's anchors by level, those of one level by their own
+// anchor (renumbers janc and anchors), and cut the list into trees, one per
+// character: false, with nothing changed, when some tree is too large for one
+// workgroup's LDS or deeper than level by level pays.
+bool plant_trees(const Packing &pk, std::vector<int32_t> &janc, std::vector<int32_t> &anchors,
+                 std::vector<hs::MPTree> &trees, std::vector<int32_t> &lev, std::vector<int2> &kids)
+{
+    const size_t na = anchors.size();
+    std::vector<int32_t> depth(na), renamed(na), order(na), up(na), first(na + 1, 0), below(na);
+    for (size_t k = 0; k < na; ++k) {
+        up[k] = janc[anchors[k]];  // an earlier one: anchors come in joint order
+        depth[k] = up[k] < 0 ? 0 : depth[up[k]] + 1;
+        if (up[k] >= 0) ++first[up[k] + 1];
+    }
+    for (size_t k = 0; k < na; ++k) first[k + 1] += first[k];
+    {
+        std::vector<int32_t> next(first.begin(), first.end() - 1);
+        for (size_t k = 0; k < na; ++k)
+            if (up[k] >= 0) below[next[up[k]]++] = (int32_t)k;
+    }
+    size_t i = 0;
+    for (size_t b = 0; b < pk.mpb.size();) {
+        // the character's joints, and its anchors
+        size_t e = b;
+        while (e < pk.mpb.size() && pk.mpb[e].chr == pk.mpb[b].chr) ++e;
+        const int64_t end = pk.mpb[e - 1].cbegin + pk.mpb[e - 1].count;
+        b = e;
+        const size_t begin = i;
+        int levels = 0;
+        for (; i < na && anchors[i] < end; ++i) levels = std::max(levels, depth[i] + 1);
+        if (i == begin) continue;
+        if (i - begin > (size_t)hs::kTreeMaxAnchors || levels > hs::kTreeMaxLevels) return false;
+        trees.push_back({(int32_t)begin, (int32_t)(i - begin), (int32_t)lev.size(), levels});
+        // breadth first: the roots, then what lies below each in turn
+        size_t at = begin;
+        for (size_t k = begin; k < i; ++k)
+            if (up[k] < 0) order[at++] = (int32_t)k;
+        int level = -1;
+        for (size_t k = begin; k < i; ++k) {
+            const int32_t o = order[k];
+            if (depth[o] != level) {
+                level = depth[o];
+                lev.push_back((int32_t)(k - begin));
+            }
+            renamed[o] = (int32_t)k;
+            for (int32_t c = first[o]; c < first[o + 1]; ++c) order[at++] = below[c];
+        }
+        lev.push_back((int32_t)(i - begin));
+    }
+    std::vector<int32_t> sorted(na);
+    for (size_t k = 0; k < na; ++k) sorted[k] = anchors[order[k]];
+    anchors.swap(sorted);
+    for (int32_t &j : janc)
+        if (j >= 0) j = renamed[j];
+    kids.assign(na, make_int2(0, 0));
+    for (size_t k = 0; k < na; ++k) {
+        const int32_t o = order[k], n = first[o + 1] - first[o];
+        kids[k] = make_int2(n > 0 ? renamed[below[first[o]]] : 0, n | depth[o] << 16);
+    }
+    return true;
 }
 
 // Upload a packing's multipass blocks and anchors and allocate the path's
@@ -833,6 +935,12 @@ hs_status make_mpset(MPSet &m, const hs_plan *plan, const Packing &pk, bool adjo
     std::vector<int32_t> janc, anchors;
     build_anchors(plan, pk, janc, anchors, m.rounds);
     m.num_anchors = (int32_t)anchors.size();
+    std::vector<hs::MPTree> trees;
+    std::vector<int32_t> lev;
+    std::vector<int2> kids;
+    if (m.rounds > 0 && !plant_trees(pk, janc, anchors, trees, lev, kids)) trees.clear();
+    m.num_trees = (int32_t)trees.size();
+    for (const hs::MPTree &t : trees) m.tree_anchors = std::max(m.tree_anchors, t.count);
     std::vector<int32_t> aself((size_t)pk.nmp, -1);
     for (size_t i = 0; i < anchors.size(); ++i) aself[anchors[i]] = (int32_t)i;
     // Segments for the in-LDS anchor rounds: a cut before anchor k is valid
@@ -863,24 +971,68 @@ hs_status make_mpset(MPSet &m, const hs_plan *plan, const Packing &pk, bool adjo
         if (aseg.size() < 2 || m.rounds == 0) aseg.clear();
         m.num_aseg = aseg.empty() ? 0 : (int32_t)aseg.size() - 1;
     }
-    hipError_t err = upload(&m.d_blocks, pk.mpb);
-    if (err == hipSuccess) err = upload(&m.d_aseg, aseg);
-    if (err == hipSuccess) err = upload(&m.d_janc, janc);
-    if (err == hipSuccess) err = upload(&m.d_aself, aself);
-    const size_t n = (size_t)pk.nmp, na = std::max<size_t>(1, anchors.size());
-    if (err == hipSuccess) err = hipMalloc(&m.A1, na * 3 * sizeof(float4));
-    if (err == hipSuccess) err = hipMalloc(&m.E1, na * sizeof(int32_t));
-    for (int i = 0; i < 2 && err == hipSuccess; ++i) {
-        err = hipMalloc(&m.AP[i], na * 3 * sizeof(float4));
-        if (err == hipSuccess) err = hipMalloc(&m.AE[i], na * sizeof(int32_t));
-        if (adjoint && err == hipSuccess) err = hipMalloc(&m.S[i], na * 3 * sizeof(float4));
+    const size_t na = std::max<size_t>(1, anchors.size());
+    std::vector<int32_t> e1(na, -1), none(na, -1), hfirst, hanc;
+    for (size_t i = 0; i < anchors.size(); ++i) e1[i] = janc[anchors[i]];
+    if (adjoint) {
+        // the heads (a parent in another block: the joint's anchor), by
+        // anchor; each head's entry of janc names its row of H instead
+        std::vector<int32_t> heads;
+        hfirst.assign(na + 1, 0);
+        for (const MPBlock &bd : pk.mpb)
+            for (int l = 0; l < bd.count; ++l) {
+                const int32_t p = plan->h_gparent[bd.gbegin + l];
+                if (p >= 0 && p < bd.gbegin) {
+                    heads.push_back((int32_t)(bd.cbegin + l));
+                    ++hfirst[janc[bd.cbegin + l] + 1];
+                }
+            }
+        for (size_t i = 0; i < na; ++i) hfirst[i + 1] += hfirst[i];
+        std::vector<int32_t> next(hfirst);
+        hanc.resize(heads.size());
+        for (int32_t c : heads) {
+            const int32_t row = next[janc[c]]++;
+            hanc[row] = janc[c];
+            janc[c] = -2 - row;
+        }
     }
-    if (adjoint && err == hipSuccess) err = hipMalloc(&m.G, n * 3 * sizeof(float4));
-    // anchor pointers start as "none": the rounds index with them, so they
-    // never hold uninitialised values (even if a validating call's check
-    // keeps the first pass from writing them)
-    if (err == hipSuccess) err = hipMemset(m.E1, 0xFF, na * sizeof(int32_t));
-    for (int i = 0; i < 2 && err == hipSuccess; ++i) err = hipMemset(m.AE[i], 0xFF, na * sizeof(int32_t));
+    Block mem;
+    const size_t o_blocks = mem.add(pk.mpb), o_aseg = mem.add(aseg), o_janc = mem.add(janc), o_aself = mem.add(aself),
+                 o_e1 = mem.add(e1), o_trees = mem.add(trees), o_lev = mem.add(lev), o_kids = mem.add(kids),
+                 o_hfirst = mem.add(hfirst), o_hanc = mem.add(hanc);
+    // the rounds go back and forth between two buffers; their pointers start
+    // as "none", since the rounds index with them
+    const int bufs = trees.empty() ? 2 : 1;
+    size_t o_ae[2] = {0, 0}, o_ap[2] = {0, 0}, o_s[2] = {0, 0};
+    for (int i = 0; i < bufs; ++i) o_ae[i] = mem.add(none);
+    const size_t o_a1 = mem.room(na * 48);
+    for (int i = 0; i < bufs; ++i) {
+        o_ap[i] = mem.room(na * 48);
+        if (adjoint) o_s[i] = mem.room(na * 48);
+    }
+    const size_t o_h = adjoint ? mem.room(hanc.size() * 48) : 0;
+    hipError_t err = mem.upload(&m.d_mem);
+    if (err == hipSuccess) {
+        m.d_blocks = at<MPBlock>(m.d_mem, o_blocks);
+        m.d_aseg = at<int32_t>(m.d_mem, o_aseg);
+        m.d_janc = at<int32_t>(m.d_mem, o_janc);
+        m.d_aself = at<int32_t>(m.d_mem, o_aself);
+        m.E1 = at<int32_t>(m.d_mem, o_e1);
+        m.d_trees = at<hs::MPTree>(m.d_mem, o_trees);
+        m.d_lev = at<int32_t>(m.d_mem, o_lev);
+        m.d_kids = at<int2>(m.d_mem, o_kids);
+        m.A1 = at<float4>(m.d_mem, o_a1);
+        for (int i = 0; i < bufs; ++i) {
+            m.AE[i] = at<int32_t>(m.d_mem, o_ae[i]);
+            m.AP[i] = at<float4>(m.d_mem, o_ap[i]);
+            if (adjoint) m.S[i] = at<float4>(m.d_mem, o_s[i]);
+        }
+        if (adjoint) {
+            m.d_hanc = at<int32_t>(m.d_mem, o_hanc);
+            m.d_hfirst = at<int32_t>(m.d_mem, o_hfirst);
+            m.H = at<float4>(m.d_mem, o_h);
+        }
+    }
     if (err != hipSuccess) {
         free_mpset(m);
         return fail_hip(err, "hs_plan_create (multipass workspace)");
@@ -1072,6 +1224,7 @@ hs_status build_paths(hs_plan *plan)
     constexpr int K = hs::kPathLen;
     const auto &off = plan->h_offsets;
     const int64_t C = plan->C, N = plan->N;
+    if (plan->num_btiles == 0) return HS_OK;  // no character of that size
     std::vector<int16_t> lane((size_t)N);  // piece of each joint, counted in its character
     std::vector<uint8_t> pos((size_t)N);   // place in the piece
     std::vector<int32_t> pieces((size_t)C, 0);
@@ -1194,20 +1347,15 @@ hs_status build_paths(hs_plan *plan)
         return HS_OK;
     std::stable_sort(tiles.begin(), tiles.end(),
                      [](const hs::PathTile &a, const hs::PathTile &b) { return a.count > b.count; });
-    // tiles (64 bytes each), lanes (16), steps (4), slots (2): in this order each is aligned
-    const size_t at_lanes = tiles.size() * sizeof(tiles[0]), at_steps = at_lanes + lanes.size() * sizeof(lanes[0]),
-                 at_slot = at_steps + steps.size() * sizeof(steps[0]);
-    std::vector<char> all(at_slot + slot.size() * sizeof(slot[0]));
-    std::memcpy(all.data(), tiles.data(), at_lanes);
-    std::memcpy(all.data() + at_lanes, lanes.data(), at_steps - at_lanes);
-    if (at_slot > at_steps) std::memcpy(all.data() + at_steps, steps.data(), at_slot - at_steps);
-    std::memcpy(all.data() + at_slot, slot.data(), all.size() - at_slot);
-    hipError_t err = upload(&P.d_tables, all);
+    Block tables;
+    const size_t o_tiles = tables.add(tiles), o_lanes = tables.add(lanes), o_steps = tables.add(steps),
+                 o_slot = tables.add(slot);
+    hipError_t err = tables.upload(&P.d_tables);
     if (err != hipSuccess) return fail_hip(err, "hs_plan_create (path adjoint)");
-    P.d_tiles = reinterpret_cast<const hs::PathTile *>(P.d_tables);
-    P.d_lanes = reinterpret_cast<const hs::PathLane *>(P.d_tables + at_lanes);
-    P.d_steps = reinterpret_cast<const uint32_t *>(P.d_tables + at_steps);
-    P.d_slot = reinterpret_cast<const uint16_t *>(P.d_tables + at_slot);
+    P.d_tiles = at<hs::PathTile>(P.d_tables, o_tiles);
+    P.d_lanes = at<hs::PathLane>(P.d_tables, o_lanes);
+    P.d_steps = at<uint32_t>(P.d_tables, o_steps);
+    P.d_slot = at<uint16_t>(P.d_tables, o_slot);
     P.h_tiles.swap(tiles);
     return HS_OK;
 }
@@ -1338,9 +1486,10 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
     // CU; measured against 512 joints: 179 vs 195 us on 10 000 x 256 joints,
     // 12 vs 20 us on 64 x 64); characters of up to 1664 joints to the
     // dataflow kernel; the rest to the multipass adjoint.
-    (void)hipFree(plan->d_btiles);
-    (void)hipFree(plan->d_bbig);
+    (void)hipFree(plan->d_adjoint);
+    plan->d_adjoint = nullptr;
     plan->d_btiles = plan->d_bbig = nullptr;
+    plan->d_bcode = nullptr;
     plan->num_btiles = plan->num_bbig = 0;
     {
         int64_t m_sync = 0;
@@ -1356,12 +1505,11 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
         plan->num_btiles = (int32_t)ps.tiles.size();
         plan->h_btiles = ps.tiles;
         // anchor codes of the adjoint tiles (the two-level adjoint)
-        (void)hipFree(plan->d_bcode);
-        plan->d_bcode = nullptr;
         plan->b_max_anchors = 0;
         plan->b_anchor_ok = false;
+        std::vector<int32_t> code;
         if (!ps.tiles.empty()) {
-            std::vector<int32_t> code((size_t)plan->N, 0);
+            code.assign((size_t)plan->N, 0);
             for (int na : all_tile_codes(plan, ps.tiles, code)) plan->b_max_anchors = std::max(plan->b_max_anchors, na);
             int w = 1;
             while (w * 64 < plan->bwd_cap) w *= 2;
@@ -1387,13 +1535,15 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
                 plan->b_bpw[kind] = bpw;
                 plan->b_one_round[kind] = r1 == 1;
             }
-            hipError_t e3 = upload(&plan->d_bcode, code);
-            if (e3 != hipSuccess) return fail_hip(e3, "hs_plan_create (adjoint codes)");
         }
         plan->num_bbig = (int32_t)pb.tiles.size();
-        hipError_t e2 = upload(&plan->d_btiles, ps.tiles);
-        if (e2 == hipSuccess) e2 = upload(&plan->d_bbig, pb.tiles);
-        if (e2 != hipSuccess) return fail_hip(e2, "hs_plan_create");
+        Block mem;
+        const size_t o_btiles = mem.add(ps.tiles), o_bbig = mem.add(pb.tiles), o_bcode = mem.add(code);
+        hipError_t e2 = mem.upload(&plan->d_adjoint);
+        if (e2 != hipSuccess) return fail_hip(e2, "hs_plan_create (adjoint tiles)");
+        plan->d_btiles = at<TileDesc>(plan->d_adjoint, o_btiles);
+        plan->d_bbig = at<TileDesc>(plan->d_adjoint, o_bbig);
+        plan->d_bcode = at<int32_t>(plan->d_adjoint, o_bcode);
         plan->bwd_untiled = pb.nmp;
         hs_status rc2 = make_mpset(plan->bmp, plan, pb, true);
         if (rc2 != HS_OK) return rc2;
@@ -1496,7 +1646,14 @@ hs::MPLaunch mp_launch(const hs_plan *p, const MPSet &m, bool validate = false)
     ml.aself = m.d_aself;
     ml.aseg = m.d_aseg;
     ml.num_aseg = m.num_aseg;
-    ml.G = m.G;
+    ml.H = m.H;
+    ml.hanc = m.d_hanc;
+    ml.hfirst = m.d_hfirst;
+    ml.trees = m.d_trees;
+    ml.num_trees = m.num_trees;
+    ml.tree_anchors = m.tree_anchors;
+    ml.lev = m.d_lev;
+    ml.kids = m.d_kids;
     for (int i = 0; i < 2; ++i) {
         ml.AP[i] = m.AP[i];
         ml.AE[i] = m.AE[i];
@@ -2039,19 +2196,18 @@ hs_status create_plan(hs_context *ctx, const hs_batch *batch, const hs_plan_opts
     plan->info.num_joints = N;
     plan->info.max_depth = max_depth;
     plan->info.max_character = max_char;
-    if ((err = upload(&plan->d_offsets, off)) != hipSuccess || (err = upload(&plan->d_parent, gparent)) != hipSuccess ||
-        (err = upload(&plan->d_level, level)) != hipSuccess) {
-        free_plan(plan);
-        return fail_hip(err, "hs_plan_create (upload)");
-    }
-
     {
-        // status word: no bits, no failing joint
-        const std::vector<uint32_t> st = {0u, 0xFFFFFFFFu};
-        if ((err = upload(&plan->d_status, st)) != hipSuccess) {
+        const std::vector<uint32_t> status = {0u, 0xFFFFFFFFu};  // no bits, no failing joint
+        Block mem;
+        const size_t o_off = mem.add(off), o_par = mem.add(gparent), o_lev = mem.add(level), o_st = mem.add(status);
+        if ((err = mem.upload(&plan->d_base)) != hipSuccess) {
             free_plan(plan);
-            return fail_hip(err, "hs_plan_create (status word)");
+            return fail_hip(err, "hs_plan_create (upload)");
         }
+        plan->d_offsets = at<int64_t>(plan->d_base, o_off);
+        plan->d_parent = at<int32_t>(plan->d_base, o_par);
+        plan->d_level = at<int32_t>(plan->d_base, o_lev);
+        plan->d_status = at<uint32_t>(plan->d_base, o_st);
     }
     if (inst) {
         plan->inst = true;

@@ -254,6 +254,19 @@ struct ChainLaunch {
     const uint32_t *gate;
 };
 
+// The anchors of one multipass character, consecutive and sorted by level
+// (those of one level by their own anchor, so that the anchors pointing to one
+// lie together).
+constexpr int kTreeMaxAnchors = 3072;  // 52 bytes of LDS each
+constexpr int kTreeMaxLevels = 64;
+struct MPTree {
+    int32_t first;      // first anchor
+    int32_t count;
+    int32_t lev_first;  // first entry of MPLaunch::lev (levels + 1 of them)
+    int32_t levels;
+};
+static_assert(sizeof(MPTree) == 16, "MPTree layout");
+
 struct MPLaunch {
     const MPBlock *blocks;
     int32_t num_blocks;
@@ -261,12 +274,13 @@ struct MPLaunch {
     const int32_t *parent;    // [N] global parent id or -1
     // anchors: the joints that are some joint's nearest out-of-block
     // ancestor; the cross-block phase jumps over these only
-    const int32_t *janc;      // [Nmp] anchor index of the joint's out-of-block ancestor, or -1
+    const int32_t *janc;      // [Nmp] anchor index of the joint's out-of-block ancestor, or -1; the
+                              // adjoint's: -2 - (its row of H) for a joint whose parent that is
     const int32_t *aself;     // [Nmp] the joint's own anchor index, or -1
     int32_t num_anchors;
     int32_t rounds;           // anchor-level jump rounds
     float4 *A1;               // [num_anchors*3] anchors' in-block products (phase 1)
-    int32_t *E1;              // [num_anchors] anchor index of each anchor's own anchor, or -1
+    const int32_t *E1;        // [num_anchors] anchor index of each anchor's own anchor, or -1
     float4 *AP[2];            // [num_anchors*3] ping-pong anchor products
     int32_t *AE[2];           // [num_anchors] ping-pong anchor pointers
     // segments of at most kAnchorSegCap consecutive anchors that no anchor
@@ -274,9 +288,18 @@ struct MPLaunch {
     // one workgroup's LDS; num_aseg = 0: rounds over all anchors in HBM
     const int32_t *aseg;
     int32_t num_aseg;
+    // instead of rounds (num_trees > 0): each character's anchors, sorted by
+    // level, level by level in one workgroup's LDS
+    const MPTree *trees;
+    int32_t num_trees;
+    int32_t tree_anchors;     // of the largest tree
+    const int32_t *lev;       // first anchor of each level, counted in the tree
+    const int2 *kids;         // [num_anchors] first anchor pointing to this one; how many | level << 16
     // adjoint workspace (NULL when the plan has none)
     float4 *S[2];             // [num_anchors*3] ping-pong anchor adjoints
-    float4 *G;                // [Nmp*3] global transforms
+    float4 *H;                // [heads*3] what each joint with its parent in another block sends there
+    const int32_t *hanc;      // [heads] the anchor that each row goes to
+    const int32_t *hfirst;    // [num_anchors + 1] first row of H that goes to each anchor
     const uint32_t *gate;     // as TileLaunch::gate
 };
 

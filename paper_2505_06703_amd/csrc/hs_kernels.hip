@@ -3227,12 +3227,126 @@ mp_local_kernel(MPLaunch ml, PoseArgs pose)
     wave_inblock_scan_lds(m, a, e, lane, slice + wv * kWave * 3, xs + 2 * wv * kWave, 3,
                           xs + (2 * wv + 1) * kWave);
     // only the anchors' in-block products leave the kernel (the output pass
-    // recomputes the others from the poses): anchor i starts the rounds from
-    // its phase-1 product and the anchor index of its own anchor
+    // recomputes the others from the poses)
     const int ai = valid ? ml.aself[cid] : -1;
-    if (ai >= 0) {
-        aff_store(ml.A1 + 3 * ai, m);
-        ml.E1[ai] = ml.janc[cid];
+    if (ai >= 0) aff_store(ml.A1 + 3 * ai, m);
+}
+
+// Both directions over the trees of anchors, level by level, instead of
+// pointer jumping: with T_a = T_e(a) P_a downward, and upward
+//     U_e = B_e + sum over the anchors a with e(a) = e of  U_a (.) P_a
+// (see the multipass adjoint), B_e the sum of the rows of H that go to e.
+// One workgroup per character and direction, its anchors' rows in LDS: one
+// composition an anchor and a barrier a level, where the rounds take a launch
+// each and, upward, atomics of hundreds of anchors on the few near the root.
+// Bound by the levels' latency (0.3 us each), so the plan takes it up to
+// kTreeMaxLevels levels.  24 characters of 3 500 to 30 000 branched joints (18
+// thousand anchors, 21 levels): 5 x 25 us of rounds upward became 18 us, the
+// downward half beside them; the adjoint call 165 -> 50 us.
+// dirs: 1 downward, 2 downward (even workgroups) and upward (odd ones).
+// LDS: rows [tree_anchors][3] f4 | (downward) the anchor pointed to
+// [tree_anchors] int | lev [kTreeMaxLevels + 1] int
+constexpr int kTreeThreads = 1024;
+
+__host__ __device__ constexpr size_t tree_lds_bytes(int anchors)
+{
+    return (size_t)anchors * 52 + (kTreeMaxLevels + 1) * 4;
+}
+
+// A workgroup barrier for LDS alone: loads from memory stay in flight over it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// u += rows[i] of i in [k, e), two rows in flight.
+__device__ __forceinline__ void add_rows(const float4 *rows, int k, int e, float u[12])
+{
+    for (; k + 1 < e; k += 2) {
+        float c0[12], c1[12];
+        aff_load(rows + 3 * (int64_t)k, c0);
+        aff_load(rows + 3 * (int64_t)(k + 1), c1);
+#pragma unroll
+        for (int r = 0; r < 12; ++r) u[r] += c0[r] + c1[r];
+    }
+    if (k < e) {
+        float c[12];
+        aff_load(rows + 3 * (int64_t)k, c);
+#pragma unroll
+        for (int r = 0; r < 12; ++r) u[r] += c[r];
+    }
+}
+
+__global__ void __launch_bounds__(kTreeThreads)
+mp_tree_kernel(MPLaunch ml, int dirs)
+{
+    extern __shared__ float4 lds[];
+    if (gated(ml.gate)) return;
+    const MPTree t = ml.trees[blockIdx.x / dirs];
+    const int tid = threadIdx.x;
+    uint32_t *link = reinterpret_cast<uint32_t *>(lds + 3 * t.count);
+    int *lev = reinterpret_cast<int *>(link + t.count);
+    for (int i = tid; i <= t.levels; i += kTreeThreads) lev[i] = ml.lev[t.lev_first + i];
+    const float4 *P = ml.A1 + 3 * (int64_t)t.first;
+    if (dirs == 1 || blockIdx.x % dirs == 0) {
+        for (int i = tid; i < t.count; i += kTreeThreads) link[i] = (uint32_t)(ml.E1[t.first + i] - t.first);
+        for (int i = tid; i < 3 * t.count; i += kTreeThreads) lds[i] = P[i];
+        __syncthreads();
+        for (int d = 1; d < t.levels; ++d) {
+            const int end = lev[d + 1];
+            for (int i = lev[d] + tid; i < end; i += kTreeThreads) {
+                float g[12], m[12];
+                aff_load(lds + 3 * link[i], g);
+                aff_load(lds + 3 * i, m);
+                aff_mul_left(g, m);
+                aff_store(lds + 3 * i, m);
+            }
+            lds_barrier();  // the level is final
+        }
+        float4 *out = ml.AP[0] + 3 * (int64_t)t.first;
+        for (int i = tid; i < 3 * t.count; i += kTreeThreads) out[i] = lds[i];
+        return;
+    }
+    // upward: a thread keeps its anchors' P and sums in registers (consecutive
+    // anchors, so a level's, on consecutive threads), so that a level waits for
+    // LDS alone; the rows hold what each anchor sends, U (.) P
+    constexpr int R = (kTreeMaxAnchors + kTreeThreads - 1) / kTreeThreads;
+    int h0[R], h1[R];
+    int2 kd[R];
+    float u[R][12], p[R][12];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = min(tid + r * kTreeThreads, t.count - 1);
+        h0[r] = ml.hfirst[t.first + i];
+        h1[r] = ml.hfirst[t.first + i + 1];
+        kd[r] = ml.kids[t.first + i];
+        aff_load(P + 3 * i, p[r]);
+        if (tid + r * kTreeThreads >= t.count) {
+            kd[r].y = -1;  // no anchor: of no level
+            h1[r] = h0[r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) u[r][k] = 0.0f;
+        add_rows(ml.H, h0[r], h1[r], u[r]);
+    }
+    for (int d = t.levels - 1; d >= 0; --d) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (kd[r].y >> 16 == d) {
+                const int i = tid + r * kTreeThreads, k = kd[r].x - t.first;
+                add_rows(lds, k, k + (kd[r].y & 0xffff), u[r]);
+                aff_store(ml.S[0] + 3 * (int64_t)(t.first + i), u[r]);
+                float c[12];
+                adj_pull(u[r], p[r], c);
+                aff_store(lds + 3 * i, c);
+            }
+        }
+        lds_barrier();  // the level has sent
     }
 }
 
@@ -3304,12 +3418,11 @@ mp_anchor_seg_kernel(const int32_t *aseg, int32_t rounds, const float4 *Pin, con
 
 // Final pass: the in-block scan again from the poses (cheaper than storing
 // and re-reading every partial), then G_j = G_anchor P_j, one composition
-// per joint.  Writes the outputs -- G through the wave's LDS slice as
-// coalesced 16-byte rows -- or (Gc non-NULL) the compact global transforms
-// the adjoint reads.  LDS: [kMPWaves][64][3] float4.
+// per joint; G leaves through the wave's LDS slice as coalesced 16-byte rows.
+// LDS: [kMPWaves][64][3] float4.
 template <bool SAMPLE>
 __global__ void __launch_bounds__(kMPWaves * kWave)
-mp_out_kernel(MPLaunch ml, PoseArgs pose, const float4 *AP, OutArgs out, float4 *Gc)
+mp_out_kernel(MPLaunch ml, PoseArgs pose, const float4 *AP, OutArgs out)
 {
     __shared__ float4 stage[kMPWaves * kWave * 3];
     __shared__ int xs[2 * kMPWaves * kWave];
@@ -3342,10 +3455,6 @@ mp_out_kernel(MPLaunch ml, PoseArgs pose, const float4 *AP, OutArgs out, float4 
         float g[12];
         aff_load(AP + 3 * an, g);
         aff_mul_left(g, m);
-    }
-    if (Gc) {
-        if (valid) aff_store(Gc + 3 * cid, m);
-        return;
     }
     if (out.global_out) {
         float4 *st = stage + wv * kWave * 3;
@@ -3687,19 +3796,19 @@ mp_chain_kernel(ChainLaunch cl, PoseArgs pose, OutArgs out)
 //     U_e = B_e + sum over anchors a with e_a = e of  U_a (.) P_a,
 //     B_e = sum over heads h with parent e of  R_B(D)_h (.) L_h,
 // the adjoint recursion again, on the anchor tree with P as the locals; and
-// X = R_B(D + U) block by block.  So: R_B(D) with heads pushing into B
-// (global float atomics, one push per head), reverse pointer jumping over
-// the anchors, then R_B(D + U) and the gradients.
+// X = R_B(D + U) block by block.  So: R_B(D), each head leaving what it sends
+// in a row of its own (sorted by anchor), the anchor trees level by level (or
+// reverse pointer jumping over them), then R_B(D + U) and the gradients.
 // ---------------------------------------------------------------------------
 // R_B for one 64-joint block held by one wave: S in (Y_j), S out (Z_j).
 // a: lane of the in-block parent, or -1.  Reverse pointer jumping over the
-// in-block ancestors with the forward doubling alongside, collisions
-// resolved with owner words as in the tiled adjoint.  Wave-private LDS:
+// in-block ancestors with the forward doubling alongside (M out: the product
+// over the lane's in-block path), collisions resolved with owner words as in
+// the tiled adjoint.  Wave-private LDS:
 // Ms[64][3], Sa[64][3] float4, Ac[64], Own[64] int.
-__device__ __forceinline__ void wave_block_reverse(float S[12], const float L[12], int a, int lane, float4 *Ms,
-                                                   float4 *Sa, int *Ac, int *Own)
+__device__ __forceinline__ void wave_block_reverse(float S[12], const float L[12], float M[12], int a, int lane,
+                                                   float4 *Ms, float4 *Sa, int *Ac, int *Own)
 {
-    float M[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) M[k] = L[k];
     aff_store(Ms + 3 * lane, M);
@@ -3748,12 +3857,14 @@ __device__ __forceinline__ void wave_block_reverse(float S[12], const float L[12
 
 constexpr int kRevWaveFloat4 = 64 * 6 + 32;  // per-wave LDS of wave_block_reverse, in float4
 
-// FINAL = false: R_B(D) per block, heads push into the anchor accumulators
-// Sanc.  FINAL = true: R_B(D + U) with U = Sanc injected at the anchors, then
-// the gradients (the parent's global transform from the compact table G).
+// FINAL = false: R_B(D) per block; each head leaves what it sends to its
+// anchor in a row of H, each anchor its in-block product in A1.  FINAL = true:
+// R_B(D + U) with U = Sanc at the anchors, and the gradients: the in-block
+// products that come with it, behind the anchors' transforms AP, are the
+// parents' global transforms.
 template <bool FINAL>
 __global__ void __launch_bounds__(kMPWaves * kWave)
-mpr_block_kernel(MPLaunch ml, PoseArgs pose, BwdArgs bwd, float4 *Sanc)
+mpr_block_kernel(MPLaunch ml, PoseArgs pose, BwdArgs bwd, const float4 *Sanc, const float4 *AP)
 {
     extern __shared__ float4 lds[];
     if (gated(ml.gate)) return;
@@ -3769,21 +3880,18 @@ mpr_block_kernel(MPLaunch ml, PoseArgs pose, BwdArgs bwd, float4 *Sanc)
     const bool valid = lane < bd.count;
     const int64_t gid = bd.gbegin + lane;
     const int64_t cid = bd.cbegin + lane;
-    int a = -1, p = -1;
-    bool head = false;
-    float L[12], S[12];
+    int a = -1, p = -1, ai = -1;
+    float L[12], S[12], M[12];
     if (valid) {
         p = ml.parent[gid];
-        if (p >= 0) {
-            if (p >= bd.gbegin) a = (int)(p - bd.gbegin); else head = true;
-        }
+        if (p >= bd.gbegin) a = (int)(p - bd.gbegin);
+        ai = ml.aself[cid];
         load_local<false>(pose, gid, 0, 0, L);
         aff_load(reinterpret_cast<const float4 *>(bwd.grad_global) + 4 * gid, S);
         if constexpr (FINAL) {
-            const int ai = ml.aself[cid];
             if (ai >= 0) {
                 float u[12];
-                aff_load(Sanc + 3 * ai, u);
+                aff_load(Sanc + 3 * (int64_t)ai, u);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) S[k] += u[k];
             }
@@ -3793,39 +3901,54 @@ mpr_block_kernel(MPLaunch ml, PoseArgs pose, BwdArgs bwd, float4 *Sanc)
 #pragma unroll
         for (int k = 0; k < 12; ++k) S[k] = 0.0f;
     }
-    wave_block_reverse(S, L, a, lane, Ms, Sa, Ac, Own);
+    wave_block_reverse(S, L, M, a, lane, Ms, Sa, Ac, Own);
     if constexpr (!FINAL) {
-        if (valid && head) {
+        const int hr = valid ? -2 - ml.janc[cid] : -1;
+        if (hr >= 0) {
             float c[12];
             adj_pull(S, L, c);
-            float *dst = reinterpret_cast<float *>(Sanc + 3 * (int64_t)ml.janc[cid]);
-#pragma unroll
-            for (int k = 0; k < 12; ++k) atomicAdd(dst + k, c[k]);
+            aff_store(ml.H + 3 * (int64_t)hr, c);
         }
-    } else if (valid) {
-        float Ap[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f};
-        if (p >= 0) {
-            float g[12];
-            aff_load(ml.G + 3 * (bd.cbegin + (p - bd.gbegin)), g);  // same character
+        if (ai >= 0) aff_store(ml.A1 + 3 * (int64_t)ai, M);
+    } else {
+        int an = valid ? ml.janc[cid] : -1;
+        if (an < -1) an = ml.hanc[-2 - an];
+        float g[12];  // the anchor's transform, then (behind the in-block product) the joint's
+        if (an >= 0) aff_load(AP + 3 * (int64_t)an, g);
+        else aff_identity(g);
+        float Ap[9] = {g[0], g[1], g[2], g[4], g[5], g[6], g[8], g[9], g[10]};  // a head's parent is its anchor
+        if (an >= 0) aff_mul_left(g, M);
+        aff_store(Ms + 3 * lane, M);
+        wave_sync();
+        if (a >= 0) {
+            aff_load(Ms + 3 * a, g);
             Ap[0] = g[0]; Ap[1] = g[1]; Ap[2] = g[2];
             Ap[3] = g[4]; Ap[4] = g[5]; Ap[5] = g[6];
             Ap[6] = g[8]; Ap[7] = g[9]; Ap[8] = g[10];
         }
-        const float4 q = reinterpret_cast<const float4 *>(pose.quat)[gid];
-        float sx = 1.0f, sy = 1.0f, sz = 1.0f;
-        if (pose.scale) {
-            const float *sp = pose.scale + 3 * gid;
-            sx = sp[0]; sy = sp[1]; sz = sp[2];
+        if (valid) {
+            const float4 q = reinterpret_cast<const float4 *>(pose.quat)[gid];
+            float sx = 1.0f, sy = 1.0f, sz = 1.0f;
+            if (pose.scale) {
+                const float *sp = pose.scale + 3 * gid;
+                sx = sp[0]; sy = sp[1]; sz = sp[2];
+            }
+            write_grads(bwd, gid, S, Ap, q, sx, sy, sz);
         }
-        write_grads(bwd, gid, S, Ap, q, sx, sy, sz);
     }
 }
 
+// B_e: the rows of H that go to each anchor, summed.
 __global__ void __launch_bounds__(256)
-mpr_fill_zero_kernel(int64_t n4, float4 *dst)
+mpr_gather_kernel(int32_t na, const int32_t *hfirst, const float4 *H, float4 *S)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n4) dst[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= na) return;
+    float u[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) u[k] = 0.0f;
+    add_rows(H, hfirst[i], hfirst[i + 1], u);
+    aff_store(S + 3 * (int64_t)i, u);
 }
 
 __global__ void __launch_bounds__(256)
@@ -4166,6 +4289,10 @@ hipError_t prepare_kernels()
         (err = hipFuncSetAttribute(reinterpret_cast<const void *>(vertex_skin_kernel<1>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSkinJoints * 32)) != hipSuccess)
         return err;
+    if ((err = hipFuncSetAttribute(reinterpret_cast<const void *>(mp_tree_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)tree_lds_bytes(kTreeMaxAnchors))) != hipSuccess)
+        return err;
     if ((err = hipFuncSetAttribute(reinterpret_cast<const void *>(mpr_anchor_seg_kernel),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)mpr_seg_lds_bytes())) != hipSuccess)
         return err;
@@ -4248,8 +4375,43 @@ hipError_t launch_forward_tiles(const TileLaunch &tl, const PoseArgs &pose, cons
 
 // Phase 1 per block, anchor rounds, final pass; Gc non-NULL: compact global
 // transforms for the adjoint instead of the outputs.
-hipError_t run_multipass(const MPLaunch &ml, const PoseArgs &pose, const OutArgs &out, float4 *Gc,
-                         hipStream_t stream)
+// The anchors' transforms from their phase-1 products (A1), into *AP; both:
+// the adjoint's sums over the anchors too, from H into S[0], where the trees do
+// them in the same launch.
+hipError_t run_anchors(const MPLaunch &ml, bool both, const float4 **AP, hipStream_t stream)
+{
+    // with no rounds the phase-1 products are final
+    *AP = ml.A1;
+    if (ml.num_anchors == 0) return hipSuccess;
+    // downward alone, rounds of pointer jumping in LDS are the quicker ones
+    // where the anchors are few enough
+    if (ml.num_trees > 0 && (both || ml.num_aseg == 0)) {
+        const int dirs = both ? 2 : 1;
+        hipLaunchKernelGGL(mp_tree_kernel, dim3((unsigned)ml.num_trees * dirs), dim3(kTreeThreads),
+                           tree_lds_bytes(ml.tree_anchors), stream, ml, dirs);
+        *AP = ml.AP[0];
+        return hipGetLastError();
+    }
+    if (ml.num_aseg > 0) {
+        hipLaunchKernelGGL(mp_anchor_seg_kernel, dim3((unsigned)ml.num_aseg), dim3(kAnchorSegCap), 0, stream,
+                           ml.aseg, ml.rounds, ml.A1, ml.E1, ml.AP[0], ml.AE[0]);
+        *AP = ml.AP[0];
+        return hipGetLastError();
+    }
+    const int32_t *ein = ml.E1;
+    const dim3 agrid((unsigned)((ml.num_anchors + 255) / 256));
+    for (int r = 0; r < ml.rounds; ++r) {
+        hipLaunchKernelGGL(mp_anchor_round_kernel, agrid, dim3(256), 0, stream, ml.num_anchors, *AP, ein, ml.AP[r & 1],
+                           ml.AE[r & 1]);
+        hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        *AP = ml.AP[r & 1];
+        ein = ml.AE[r & 1];
+    }
+    return hipSuccess;
+}
+
+hipError_t run_multipass(const MPLaunch &ml, const PoseArgs &pose, const OutArgs &out, hipStream_t stream)
 {
     const dim3 blk(kMPWaves * kWave);
     const dim3 grid((ml.num_blocks + kMPWaves - 1) / kMPWaves);
@@ -4259,29 +4421,12 @@ hipError_t run_multipass(const MPLaunch &ml, const PoseArgs &pose, const OutArgs
         hipLaunchKernelGGL(mp_local_kernel<false>, grid, blk, 0, stream, ml, pose);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    // rounds over the anchors, from the phase-1 products (A1, E1) into the
-    // ping-pong buffers; with no rounds the phase-1 products are final
-    const float4 *pin = ml.A1;
-    const int32_t *ein = ml.E1;
-    if (ml.num_anchors > 0 && ml.num_aseg > 0) {
-        hipLaunchKernelGGL(mp_anchor_seg_kernel, dim3((unsigned)ml.num_aseg), dim3(kAnchorSegCap), 0, stream,
-                           ml.aseg, ml.rounds, ml.A1, ml.E1, ml.AP[0], ml.AE[0]);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-        pin = ml.AP[0];
-    } else if (ml.num_anchors > 0) {
-        const dim3 agrid((unsigned)((ml.num_anchors + 255) / 256));
-        for (int r = 0; r < ml.rounds; ++r) {
-            hipLaunchKernelGGL(mp_anchor_round_kernel, agrid, dim3(256), 0, stream, ml.num_anchors, pin, ein,
-                               ml.AP[r & 1], ml.AE[r & 1]);
-            if ((err = hipGetLastError()) != hipSuccess) return err;
-            pin = ml.AP[r & 1];
-            ein = ml.AE[r & 1];
-        }
-    }
+    const float4 *ap = nullptr;
+    if ((err = run_anchors(ml, false, &ap, stream)) != hipSuccess) return err;
     if (pose.kind == 1)
-        hipLaunchKernelGGL(mp_out_kernel<true>, grid, blk, 0, stream, ml, pose, pin, out, Gc);
+        hipLaunchKernelGGL(mp_out_kernel<true>, grid, blk, 0, stream, ml, pose, ap, out);
     else
-        hipLaunchKernelGGL(mp_out_kernel<false>, grid, blk, 0, stream, ml, pose, pin, out, Gc);
+        hipLaunchKernelGGL(mp_out_kernel<false>, grid, blk, 0, stream, ml, pose, ap, out);
     return hipGetLastError();
 }
 
@@ -4312,7 +4457,7 @@ hipError_t launch_forward_multipass(const MPLaunch &ml, const PoseArgs &pose, co
                                     hipStream_t stream)
 {
     if (ml.num_blocks == 0) return hipSuccess;
-    return run_multipass(ml, pose, out, nullptr, stream);
+    return run_multipass(ml, pose, out, stream);
 }
 
 hipError_t launch_pose_sample(const TileLaunch &tl, const MPLaunch &ml, const ChainLaunch &cl, const PoseArgs &pose,
@@ -4761,47 +4906,49 @@ hipError_t launch_backward_multipass(const MPLaunch &ml, const PoseArgs &pose, c
                                      hipStream_t stream)
 {
     if (ml.num_blocks == 0) return hipSuccess;
-    if (!ml.G || !ml.aself || (ml.num_anchors > 0 && !ml.S[0])) return hipErrorNotSupported;
+    if (!ml.aself || !ml.hanc || (ml.num_anchors > 0 && !ml.S[0])) return hipErrorNotSupported;
     if (bwd.eff_ids) return hipErrorInvalidValue;  // sparse seeds: synchronous tiles only
     const dim3 blk(kMPWaves * kWave);
     const dim3 grid((ml.num_blocks + kMPWaves - 1) / kMPWaves);
     const size_t lds = (size_t)kMPWaves * kRevWaveFloat4 * sizeof(float4);
-    hipError_t err;
-    // global transforms of the multipass characters (compact), and P
-    if ((err = run_multipass(ml, pose, OutArgs{}, ml.G, stream)) != hipSuccess) return err;
     const int na = ml.num_anchors;
-    const dim3 agrid((unsigned)((na + 255) / 256));
-    const dim3 cgrid((unsigned)((3 * (int64_t)na + 255) / 256));
+    hipLaunchKernelGGL(mpr_block_kernel<false>, grid, blk, lds, stream, ml, pose, bwd, (const float4 *)nullptr,
+                       (const float4 *)nullptr);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    // the anchors' transforms and, with trees, their adjoints
+    const float4 *ap = nullptr;
     int cur = 0;
-    if (na > 0) {
-        hipLaunchKernelGGL(mpr_fill_zero_kernel, cgrid, dim3(256), 0, stream, 3 * (int64_t)na, ml.S[0]);
+    if (na > 0 && ml.num_trees == 0) {
+        hipLaunchKernelGGL(mpr_gather_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, stream, na, ml.hfirst,
+                           ml.H, ml.S[0]);
         if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-    hipLaunchKernelGGL(mpr_block_kernel<false>, grid, blk, lds, stream, ml, pose, bwd, ml.S[0]);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    if (na > 0 && ml.num_aseg > 0) {
-        // per segment in one workgroup's LDS, from the phase-1 products and
-        // pointers (A1, E1, left by the forward pass above); in place in S[0]
-        hipLaunchKernelGGL(mpr_anchor_seg_kernel, dim3((unsigned)ml.num_aseg), dim3(kAnchorSegCap),
-                           mpr_seg_lds_bytes(), stream, ml.aseg, ml.rounds, ml.S[0], ml.A1, ml.E1);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    } else if (na > 0) {
-        // the anchors' phase-1 products and pointers (A1, E1, left by the
-        // forward pass above) start the reverse rounds
-        const float4 *min = ml.A1;
-        const int32_t *ein = ml.E1;
-        for (int r = 0; r < ml.rounds; ++r) {
-            hipLaunchKernelGGL(mpr_copy_kernel, cgrid, dim3(256), 0, stream, 3 * (int64_t)na, ml.S[cur], ml.S[cur ^ 1]);
+        if (ml.num_aseg > 0) {
+            // per segment in one workgroup's LDS, from the phase-1 products
+            // and pointers; in place in S[0]
+            hipLaunchKernelGGL(mpr_anchor_seg_kernel, dim3((unsigned)ml.num_aseg), dim3(kAnchorSegCap),
+                               mpr_seg_lds_bytes(), stream, ml.aseg, ml.rounds, ml.S[0], ml.A1, ml.E1);
             if ((err = hipGetLastError()) != hipSuccess) return err;
-            hipLaunchKernelGGL(mpr_anchor_round_kernel, agrid, dim3(256), 0, stream, na, ml.S[cur], min, ein,
-                               ml.S[cur ^ 1], ml.AP[r & 1], ml.AE[r & 1]);
-            if ((err = hipGetLastError()) != hipSuccess) return err;
-            min = ml.AP[r & 1];
-            ein = ml.AE[r & 1];
-            cur ^= 1;
+        } else {
+            const dim3 agrid((unsigned)((na + 255) / 256));
+            const dim3 cgrid((unsigned)((3 * (int64_t)na + 255) / 256));
+            const float4 *min = ml.A1;
+            const int32_t *ein = ml.E1;
+            for (int r = 0; r < ml.rounds; ++r) {
+                hipLaunchKernelGGL(mpr_copy_kernel, cgrid, dim3(256), 0, stream, 3 * (int64_t)na, ml.S[cur],
+                                   ml.S[cur ^ 1]);
+                if ((err = hipGetLastError()) != hipSuccess) return err;
+                hipLaunchKernelGGL(mpr_anchor_round_kernel, agrid, dim3(256), 0, stream, na, ml.S[cur], min, ein,
+                                   ml.S[cur ^ 1], ml.AP[r & 1], ml.AE[r & 1]);
+                if ((err = hipGetLastError()) != hipSuccess) return err;
+                min = ml.AP[r & 1];
+                ein = ml.AE[r & 1];
+                cur ^= 1;
+            }
         }
     }
-    hipLaunchKernelGGL(mpr_block_kernel<true>, grid, blk, lds, stream, ml, pose, bwd, ml.S[cur]);
+    if ((err = run_anchors(ml, true, &ap, stream)) != hipSuccess) return err;
+    hipLaunchKernelGGL(mpr_block_kernel<true>, grid, blk, lds, stream, ml, pose, bwd, (const float4 *)ml.S[cur], ap);
     return hipGetLastError();
 }
 
