@@ -55,6 +55,25 @@ struct Range {
     const char *name;
 };
 
+// A call's arrays, without an allocation (no call has more than a dozen).
+struct Ranges {
+    Range r[16];
+    size_t n = 0;
+    Ranges() = default;
+    Ranges(std::initializer_list<Range> list)
+    {
+        for (const Range &x : list) push_back(x);
+    }
+    void push_back(const Range &x)
+    {
+        if (n < 16) r[n++] = x;
+    }
+    size_t size() const { return n; }
+    const Range &operator[](size_t i) const { return r[i]; }
+    const Range *begin() const { return r; }
+    const Range *end() const { return r + n; }
+};
+
 bool overlap(const Range &a, const Range &b)
 {
     if (!a.p || !b.p || a.bytes == 0 || b.bytes == 0) return false;
@@ -63,7 +82,7 @@ bool overlap(const Range &a, const Range &b)
 }
 
 // Every output must be disjoint from every input and from the other outputs.
-hs_status check_aliasing(const std::vector<Range> &outs, const std::vector<Range> &ins)
+hs_status check_aliasing(const Ranges &outs, const Ranges &ins)
 {
     for (size_t i = 0; i < outs.size(); ++i) {
         for (const Range &in : ins)
@@ -568,16 +587,18 @@ void free_plan(hs_plan *p)
 // RAII guard that makes the plan's device current for the duration of a call.
 struct DeviceGuard {
     int prev = -1;
-    bool ok = true;
+    bool ok = true, changed = false;
     explicit DeviceGuard(int dev)
     {
         if (hipGetDevice(&prev) != hipSuccess) prev = -1;
-        if (prev != dev) ok = hipSetDevice(dev) == hipSuccess;
+        if (prev != dev) {
+            ok = hipSetDevice(dev) == hipSuccess;
+            changed = ok;
+        }
     }
     ~DeviceGuard()
     {
-        int cur = -1;
-        if (prev >= 0 && hipGetDevice(&cur) == hipSuccess && cur != prev) (void)hipSetDevice(prev);
+        if (changed && prev >= 0) (void)hipSetDevice(prev);
     }
 };
 
@@ -1691,7 +1712,7 @@ hs_status launch_validate(const hs_plan *plan, hipStream_t stream, const char *w
 }
 
 hs_status check_pose_src(const hs_plan *plan, const hs_pose_src *src, hs::PoseArgs &pa,
-                         std::vector<Range> &ins, bool allow_clips)
+                         Ranges &ins, bool allow_clips)
 {
     if (!src) return fail(HS_ERR_INVALID_ARG, "pose source is NULL");
     const size_t N = (size_t)plan->N;
@@ -1951,14 +1972,14 @@ hs_status prepare_forward(const hs_plan *plan, const hs_pose_src *src, float *gl
     for (const void *p : {(const void *)global_out, (const void *)inv_bind, (const void *)skin_out,
                           (const void *)ckpt_out})
         if (p && !aligned(p, 16)) return fail(HS_ERR_INVALID_ARG, "hs_scan_forward: outputs and inv_bind must be 16-byte aligned");
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, src, pa, ins, true);
     if (rc != HS_OK) return rc;
     if (plan->shape.algorithm != HS_ALG_SCAN && src->kind != HS_POSE_TRS)
         return fail(HS_ERR_UNSUPPORTED, "hs_scan_forward: the paper's algorithms take stored TRS poses only");
     const size_t N = (size_t)plan->N;
     ins.push_back({inv_bind, (plan->inst ? (size_t)plan->skel_joints : N) * 64, "inv_bind"});
-    std::vector<Range> outs = {{global_out, N * 64, "global_out"}, {skin_out, N * 64, "skin_out"},
+    Ranges outs = {{global_out, N * 64, "global_out"}, {skin_out, N * 64, "skin_out"},
                                {ckpt_out, N * 48, "ckpt_out"}};
     if ((rc = check_aliasing(outs, ins)) != HS_OK) return rc;
     oa = hs::OutArgs{};
@@ -2483,11 +2504,11 @@ hs_status hs_pose_sample(const hs_plan *plan, const hs_clip_lib *lib, const hs_c
     src.clips = lib;
     src.params = params;
     hs::PoseArgs pa;
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, &src, pa, ins, true);
     if (rc != HS_OK) return rc;
     const size_t N = (size_t)plan->N;
-    std::vector<Range> outs = {{quat_out, N * 16, "quat_out"}, {trans_out, N * 12, "trans_out"}};
+    Ranges outs = {{quat_out, N * 16, "quat_out"}, {trans_out, N * 12, "trans_out"}};
     if ((rc = check_aliasing(outs, ins)) != HS_OK) return rc;
     if (N == 0) return HS_OK;
     DeviceGuard dg(plan->ctx->device);
@@ -2531,7 +2552,7 @@ hs_status sample_backward(const char *name, const hs_plan *plan, const hs_clip_l
     src.clips = lib;
     src.params = params;
     hs::PoseArgs pa;
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, &src, pa, ins, true);
     if (rc != HS_OK) return rc;
     const size_t N = (size_t)plan->N, C = (size_t)plan->C;
@@ -2544,7 +2565,7 @@ hs_status sample_backward(const char *name, const hs_plan *plan, const hs_clip_l
     ins.push_back({grad_quat, N * 16, "grad_quat"});
     ins.push_back({grad_trans, N * 12, "grad_trans"});
     const size_t keys = (size_t)lib->num_clips * lib->num_keys * lib->joints_per_clip;
-    std::vector<Range> outs = {{grad_key_quat, grad_key_quat ? keys * 16 : 0, "grad_key_quat"},
+    Ranges outs = {{grad_key_quat, grad_key_quat ? keys * 16 : 0, "grad_key_quat"},
                                {grad_key_trans, grad_key_trans ? keys * 12 : 0, "grad_key_trans"},
                                {grad_time, grad_time ? C * 4 : 0, "grad_time"},
                                {grad_weight, grad_weight ? C * 4 : 0, "grad_weight"},
@@ -2591,7 +2612,7 @@ hs_status hs_stream_probe(int64_t n, const float *quat, const float *trans, cons
     if (!aligned(quat, 16) || !aligned(out, 16) || !aligned(trans, 4) || !aligned(scale, 4) || !aligned(table, 4))
         return fail(HS_ERR_INVALID_ARG, "hs_stream_probe: quat and out must be 16-byte aligned, the rest 4");
     const size_t N = (size_t)n;
-    std::vector<Range> ins = {{quat, N * 16, "quat"}, {trans, N * 12, "trans"}, {scale, N * 12, "scale"},
+    Ranges ins = {{quat, N * 16, "quat"}, {trans, N * 12, "trans"}, {scale, N * 12, "scale"},
                               {table, N * 4, "table"}};
     hs_status rc = check_aliasing({{out, N * 64, "out"}}, ins);
     if (rc != HS_OK) return rc;
@@ -2848,7 +2869,7 @@ hs_status hs_scan_skin_vertices(const hs_plan *plan, const hs_pose_src *src, con
         return fail(HS_ERR_UNSUPPORTED, "hs_scan_skin_vertices: tiles of at most %d joints (plan has %d)",
                     hs::kMaxVertexTileJoints, plan->shape.tile_cap);
     hs::PoseArgs pa;
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, src, pa, ins, true);
     if (rc != HS_OK) return rc;
     const size_t N = (size_t)plan->N, V = (size_t)mesh->V;
@@ -2858,7 +2879,7 @@ hs_status hs_scan_skin_vertices(const hs_plan *plan, const hs_pose_src *src, con
     if (!aligned(inv_bind, 16) || !aligned(skin_out, 16) || !aligned(vertices_out, 4))
         return fail(HS_ERR_INVALID_ARG, "hs_scan_skin_vertices: inv_bind and skin_out must be 16-byte aligned");
     ins.push_back({inv_bind, (plan->inst ? (size_t)plan->skel_joints : N) * 64, "inv_bind"});
-    std::vector<Range> outs = {{vertices_out, V * 12, "vertices_out"}, {skin_out, skin_out ? N * 64 : 0, "skin_out"}};
+    Ranges outs = {{vertices_out, V * 12, "vertices_out"}, {skin_out, skin_out ? N * 64 : 0, "skin_out"}};
     if ((rc = check_aliasing(outs, ins)) != HS_OK) return rc;
     DeviceGuard dg(plan->ctx->device);
     if (!dg.ok) return fail(HS_ERR_DEVICE, "hs_scan_skin_vertices: cannot select device");
@@ -2890,13 +2911,13 @@ hs_status hs_scan_backward(const hs_plan *plan, const hs_pose_src *src, const fl
     if (!aligned(grad_trans, 4) || (grad_scale && !aligned(grad_scale, 4)))
         return fail(HS_ERR_INVALID_ARG, "hs_scan_backward: grad_trans/grad_scale must be 4-byte aligned");
     hs::PoseArgs pa;
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, src, pa, ins, false);
     if (rc != HS_OK) return rc;
     const size_t N = (size_t)plan->N;
     ins.push_back({grad_global, N * 64, "grad_global"});
     ins.push_back({ckpt, ckpt ? N * 48 : 0, "ckpt"});
-    std::vector<Range> outs = {{grad_quat, N * 16, "grad_quat"}, {grad_trans, N * 12, "grad_trans"},
+    Ranges outs = {{grad_quat, N * 16, "grad_quat"}, {grad_trans, N * 12, "grad_trans"},
                                {grad_scale, grad_scale ? N * 12 : 0, "grad_scale"}};
     if ((rc = check_aliasing(outs, ins)) != HS_OK) return rc;
     if (N == 0) return HS_OK;
@@ -3049,12 +3070,12 @@ hs_status hs_effector_backward(const hs_plan *plan, const hs_effectors *effector
     if (!aligned(targets, 4) || !aligned(grad_trans, 4) || (grad_scale && !aligned(grad_scale, 4)))
         return fail(HS_ERR_INVALID_ARG, "hs_effector_backward: targets/grad_trans/grad_scale must be 4-byte aligned");
     hs::PoseArgs pa;
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, src, pa, ins, false);
     if (rc != HS_OK) return rc;
     ins.push_back({global, N * 64, "global"});
     ins.push_back({targets, E * 12, "targets"});
-    std::vector<Range> outs = {{grad_quat, N * 16, "grad_quat"}, {grad_trans, N * 12, "grad_trans"},
+    Ranges outs = {{grad_quat, N * 16, "grad_quat"}, {grad_trans, N * 12, "grad_trans"},
                                {grad_scale, grad_scale ? N * 12 : 0, "grad_scale"}};
     if ((rc = check_aliasing(outs, ins)) != HS_OK) return rc;
     DeviceGuard dg(plan->ctx->device);
@@ -3100,11 +3121,11 @@ hs_status hs_effector_step(const hs_plan *plan, const hs_effectors *effectors, c
     if (!aligned(targets, 4) || !aligned(grad_trans, 4) || (grad_scale && !aligned(grad_scale, 4)))
         return fail(HS_ERR_INVALID_ARG, "hs_effector_step: targets/grad_trans/grad_scale must be 4-byte aligned");
     hs::PoseArgs pa;
-    std::vector<Range> ins;
+    Ranges ins;
     hs_status rc = check_pose_src(plan, src, pa, ins, false);
     if (rc != HS_OK) return rc;
     ins.push_back({targets, E * 12, "targets"});
-    std::vector<Range> outs = {{global_out, global_out ? N * 64 : 0, "global_out"},
+    Ranges outs = {{global_out, global_out ? N * 64 : 0, "global_out"},
                                {grad_quat, N * 16, "grad_quat"}, {grad_trans, N * 12, "grad_trans"},
                                {grad_scale, grad_scale ? N * 12 : 0, "grad_scale"}};
     if ((rc = check_aliasing(outs, ins)) != HS_OK) return rc;

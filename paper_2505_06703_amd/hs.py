@@ -252,15 +252,20 @@ def hs_version():
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None and torch.cuda.is_initialized():
+        # the current device's current stream, without a Stream object for it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _need(t, name, shape, dtype=torch.float32):
+    # the usual case first: the checks below are most of a small call's host time
+    if type(t) is torch.Tensor and t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
