@@ -126,7 +126,8 @@ typedef struct hs_batch {
 
 typedef struct hs_plan_opts {
     int32_t strategy;       /* HS_STRATEGY_* */
-    int32_t tile_joints;    /* tile capacity in joints (multiple of 64), 0 = choose */
+    int32_t tile_joints;    /* tile capacity in joints (multiple of 64), 0 = choose: up to the
+                             * largest character's size, or up to 256 joints if that is more */
     int32_t waves_per_tile; /* 64-lane waves per workgroup (1..16), 0 = choose */
     int32_t grid_tiles;     /* workgroups launched: 0 = one per tile; k > 0 = k per CU, each
                                looping over the cost-sorted tiles */
@@ -152,14 +153,12 @@ typedef struct hs_plan_opts {
  * resident workgroups per CU, each walking the list with a static stride;
  * LDS holds only the transforms of each tile's anchors (joints whose
  * children lie in another 64-joint block) and one staging slice per wave,
- * so large tiles do not cost occupancy.  Without tile_joints the queue's
- * tiles hold the largest character, at least 256 joints.  HS_SCHED_CLASSES:
- * one launch per size class (characters of up to 1024 joints, up to 1664,
- * the rest) with all of a tile's transforms in LDS.  HS_SCHED_AUTO takes the
- * queue where it applies (the library's scan, no chain units, not
- * instanced, a tile strategy, and each tile's anchors within the LDS) and
- * the classes elsewhere; HS_SCHED_QUEUE where it does not apply is
- * HS_ERR_UNSUPPORTED. */
+ * so large tiles do not cost occupancy.  HS_SCHED_CLASSES: one launch per
+ * size class (characters of up to 1024 joints, up to 1664, the rest) with
+ * all of a tile's transforms in LDS.  HS_SCHED_AUTO takes the queue where it
+ * applies (the library's scan, no chain units, not instanced, a tile
+ * strategy, and each tile's anchors within the LDS) and the classes
+ * elsewhere; HS_SCHED_QUEUE where it does not apply is HS_ERR_UNSUPPORTED. */
 #define HS_SCHED_AUTO 0
 #define HS_SCHED_QUEUE 1
 #define HS_SCHED_CLASSES 2

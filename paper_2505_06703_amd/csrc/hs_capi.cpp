@@ -221,7 +221,6 @@ struct Shape {
     int algorithm = HS_ALG_SCAN;
     int adjoint = HS_ADJ_ROUNDS;
     int queue_waves = 0;  // > 0: the forward runs as one work-queue launch with this many waves
-    int queue_cap = 0;    // work queue: tile capacity when it differs from tile_cap (0: tile_cap)
 };
 
 } // namespace
@@ -1407,7 +1406,7 @@ hs_status build_queue(hs_plan *plan, const Shape &shape, int strategy, bool *bui
     Q.d_tiles = nullptr;
     Q.d_code = nullptr;
     Q.num_tiles = Q.grid = Q.max_anchors = 0;
-    const int cap = shape.queue_cap > 0 ? shape.queue_cap : shape.tile_cap;
+    const int cap = shape.tile_cap;
     const Packing pk = pack_tiles(plan, cap, strategy, false, 0, cap);
     std::vector<hs::QTile> qt(pk.tiles.size());
     std::vector<int32_t> code((size_t)plan->N, 0);
@@ -1848,7 +1847,6 @@ hs_status autotune(hs_plan *plan, const Shape &base, int strategy)
                 for (int g : {0, 64}) {
                     Shape c = base;
                     c.tile_cap = cap;
-                    c.queue_cap = 0;
                     c.queue_waves = w;
                     c.grid_per_cu = g;
                     while (c.waves > 1 && c.waves * 64 > cap) c.waves >>= 1;  // the size-class tiles' waves
@@ -2249,6 +2247,14 @@ hs_status create_plan(hs_context *ctx, const hs_batch *batch, const hs_plan_opts
     } else {
         const int64_t target = (N + 2 * (int64_t)ctx->num_cu - 1) / (2 * (int64_t)ctx->num_cu);
         sh.tile_cap = (int)std::min<int64_t>(1024, round_up((int)std::max<int64_t>(64, target), 64));
+        // no larger than the largest character needs, from 256 joints on: small
+        // workgroups, several of them on a CU at a time, overlap their phases
+        // (10 000 x 256 joints, scan and skinning in one pass: 102 us on
+        // 256-joint tiles, 129 on 512, 148 on 1024; two blends and skin
+        // matrices, size classes: 105 against 110; 20 000 x 40 joints, size
+        // classes: 19.2 against 23.4; 128 measures as 256)
+        if (o.algorithm == HS_ALG_SCAN && !o.chain_units)
+            sh.tile_cap = std::min(sh.tile_cap, std::max(256, min_cap));
         sh.tile_cap = std::max(sh.tile_cap, std::min(min_cap, 2048));
     }
     if (hs::forward_tile_lds_bytes(sh.tile_cap, true) > ctx->max_lds || sh.tile_cap > lds_cap) {
@@ -2279,14 +2285,8 @@ hs_status create_plan(hs_context *ctx, const hs_batch *batch, const hs_plan_opts
         // four waves (measured against eight and sixteen on the deep,
         // heterogeneous and fused workloads: more workgroups per CU), fewer
         // on tiles of fewer blocks
-        // default tiles: the largest character's size, at least 256 joints
-        // (one workgroup per tile; measured on 10 000 x 256 joints with
-        // sampled poses: 88.4 us on 256-joint tiles against 93.9 us on
-        // 1024-joint ones)
-        if (o.tile_joints == 0 && sh.tile_cap > 256) sh.queue_cap = std::max(256, std::min(min_cap, sh.tile_cap));
-        const int qcap = sh.queue_cap > 0 ? sh.queue_cap : sh.tile_cap;
         int w = o.waves_per_tile > 0 ? o.waves_per_tile : 4;
-        while (w > 1 && w * 64 > qcap) w >>= 1;
+        while (w > 1 && w * 64 > sh.tile_cap) w >>= 1;
         sh.queue_waves = w;
     }
     if (sh.algorithm != HS_ALG_SCAN) {
