@@ -2679,109 +2679,166 @@ sample_bwd_kernel(PoseArgs P, SampleBwdArgs A)
 }
 
 // Keyframe gradients by gathering instead of scattering: one workgroup per
-// (clip, key) block.  Its readers are the characters that read the block as
-// clip A or B, at key k0 or k1 of their frame: up to four entries each.
-// Every thread counts the entries of its characters (scan_key_readers) in
-// one pass over the clip parameters; a workgroup prefix sum
-// gives each thread the place of its first entry, and a second pass writes
-// the entries there, so the list is in a fixed order (by thread, then by
-// character) whatever the scheduling.  Each thread then sums, for its
+// KEYS (1 or 2) consecutive keys of a clip.  Their readers are the characters
+// that use the clip as A or B with one of the keys as k0 or k1 of their
+// frame; an entry is a (character, A or B) pair, and serves both its keys if
+// both are the workgroup's.  Every thread counts the entries of its
+// characters in one pass over the clip parameters; a workgroup prefix sum
+// gives each thread the place of its first entry, and a second pass over the
+// characters that the first found (the first 16 384 characters' bits are
+// kept) writes the entries there, so the list is in a fixed order (by thread,
+// then by character) whatever the scheduling.  Each thread then sums, for its
 // joints, every reader's contribution -- (1 - alpha) or alpha s times the
 // adjoint of the key blend, (1 - alpha) or alpha times the weighted dLoss/dt
 // -- and writes its key rows once.  No atomics on the gradients, no zero
-// fill (blocks nobody reads get zeros), and the sums are bitwise
-// reproducible.  A block with more readers than the list holds takes them
-// in rounds of kKeyReaders.
-constexpr int kKeyReaders = 1024;
+// fill (keys nobody reads get zeros), and the sums are bitwise reproducible.
+// A list longer than kKeyReaders is taken in rounds.
+//
+// Bound by those reads: a reader's row is 28 bytes a joint, from the
+// last-level cache mostly.  One entry for both keys reads three rows where
+// one key a workgroup reads four; kKeyAhead rows in flight hide the latency
+// (a list that was read one entry at a time, each waited for, took 97 us on
+// 10 000 characters of 256 joints over 64 clips of 30 keys; this takes 65,
+// and 80 with one key a workgroup; 8 in flight measure as 4).
+constexpr int kKeyReaders = 1000;
+constexpr int kKeyAhead = 4;
 
-// Calls emit(entry, alpha) for each entry of character c in block (clip,
-// key), in a fixed order; entry = 4 c + 2 X + role (X: clip A or B, role:
-// key k0 or k1 of the character's frame), alpha the frame's fraction.
+// Calls emit(entry, alpha) for each entry of character c in keys
+// [key, key + nk) of the clip, in a fixed order; entry = 32 c + 16 X + 4 t1 +
+// t0, where X is the clip slot (A or B), t0 - 1 the key (from `key` on) that
+// is the character's k0 and t1 - 1 the one that is its k1 (0: neither), and
+// alpha the frame's fraction.
 template <typename Emit>
-__device__ __forceinline__ void key_block_entries(const PoseArgs &P, int c, int clip, int key, Emit &&emit)
+__device__ __forceinline__ void key_entries(const PoseArgs &P, int c, int clip, int key, int nk, Emit &&emit)
 {
     const int cl[2] = {P.clip_a[c], P.clip_b[c]};
-    if (cl[0] != clip && cl[1] != clip) return;  // most characters: two loads
     int k0, k1;
     float alpha;
     if (!sample_frame(P, c, k0, k1, alpha)) return;
+    const int t0 = k0 >= key && k0 < key + nk ? k0 - key + 1 : 0;
+    const int t1 = k1 >= key && k1 < key + nk ? k1 - key + 1 : 0;
+    if (t0 + t1 == 0) return;
 #pragma unroll
-    for (int X = 0; X < 2; ++X) {
-        if (cl[X] != clip) continue;
-        if (k0 == key) emit(4 * c + 2 * X, alpha);
-        if (k1 == key) emit(4 * c + 2 * X + 1, alpha);
-    }
+    for (int X = 0; X < 2; ++X)
+        if (cl[X] == clip) emit(32 * (int64_t)c + 16 * X + 4 * t1 + t0, alpha);
 }
 
-// This thread's readers of block (clip, key), in a fixed order: characters
-// c = seg + 256 k + thread, segment by segment.  The clip ids of a
-// segment's 16 characters are loaded together (no branch between the
-// loads, so one memory latency per segment), then only the characters
-// that use the clip are examined.
+// This thread's users of the clip among the characters seg + 256 k + thread,
+// k < 64: bit k.  The clip ids of 16 characters are loaded together (no
+// branch between the loads, so one memory latency for them).
 constexpr int kScanPer = 16;
+constexpr int kScanSeg = kSampleBwdThreads * 64;
 
-template <typename Emit>
-__device__ __forceinline__ void scan_key_readers(const PoseArgs &P, int C, int clip, int key, Emit &&emit)
+__device__ __forceinline__ uint64_t clip_users(const PoseArgs &P, int C, int clip, int64_t seg)
 {
-    for (int seg = 0; seg < C; seg += kSampleBwdThreads * kScanPer) {
-        const int c0 = seg + (int)threadIdx.x;
-        uint32_t m = 0;
+    uint64_t m = 0;
+#pragma unroll 1
+    for (int k0 = 0; k0 < 64 && seg + k0 * kSampleBwdThreads < C; k0 += kScanPer) {
+        int ca[kScanPer], cb[kScanPer];
 #pragma unroll
         for (int k = 0; k < kScanPer; ++k) {
-            const int c = c0 + k * kSampleBwdThreads;
-            const int ca = c < C ? P.clip_a[c] : -1;
-            const int cb = c < C ? P.clip_b[c] : -1;
-            m |= (uint32_t)((ca == clip) | (cb == clip)) << k;
+            const int64_t c0 = seg + (k0 + k) * kSampleBwdThreads;
+            const int last = (int)max(C - 1 - c0, (int64_t)-1);  // threads past it read some character's
+            const int64_t b = last < 0 ? 0 : c0;                 // ids and drop them
+            const uint32_t t = min((uint32_t)threadIdx.x, (uint32_t)max(last, 0));
+            ca[k] = (P.clip_a + b)[t];
+            cb[k] = (P.clip_b + b)[t];
         }
+        __builtin_amdgcn_sched_barrier(0);  // all loads before the first wait
+        uint32_t part = 0;
+#pragma unroll
+        for (int k = 0; k < kScanPer; ++k) {
+            const bool in = (int)threadIdx.x <= C - 1 - seg - (k0 + k) * kSampleBwdThreads;
+            part |= (uint32_t)(((ca[k] == clip) | (cb[k] == clip)) & in) << k;
+        }
+        m |= (uint64_t)part << k0;
+    }
+    return m;
+}
+
+// This thread's readers of keys [key, key + nk) of the clip, in a fixed
+// order: its characters, segment by segment.  `users` keeps the first
+// segment's bits from the count (`counted` false) for the passes that fill
+// the list.
+template <typename Emit>
+__device__ __forceinline__ void scan_key_readers(const PoseArgs &P, int C, int clip, int key, int nk, uint64_t &users,
+                                                 bool counted, Emit &&emit)
+{
+#pragma unroll 1
+    for (int64_t seg = 0; seg < C; seg += kScanSeg) {
+        uint64_t m = seg == 0 && counted ? users : clip_users(P, C, clip, seg);
+        if (seg == 0) users = m;
         while (m) {
-            const int k = __builtin_ctz(m);
+            const int k = __builtin_ctzll(m);
             m &= m - 1;
-            key_block_entries(P, c0 + k * kSampleBwdThreads, clip, key, emit);
+            key_entries(P, (int)(seg + k * kSampleBwdThreads + (int)threadIdx.x), clip, key, nk, emit);
         }
     }
 }
 
-// The block's reader list in LDS.  With the workspace (WS) each entry also
-// carries the reader's first joint, joint count and its two factors, the
-// key-blend factor ((1 - alpha), or alpha, which the k1 role multiplies by
-// the arc sign) and the translation factor ((1 - alpha) or alpha, times
-// 1 - w or w), so that summing an entry takes two loads.
+// The reader list in LDS: the entry without the workspace.  With it (WS)
+// 32 times the reader's first joint, plus the entry's low bits; its joint
+// count; its frame's fraction; its clip's share of the translation (1 - w or
+// w): summing an entry then takes two loads.  20 bytes an entry: eight
+// workgroups fit a CU's LDS.
 template <bool WS>
 struct KeyList {
-    int entry[kKeyReaders];
-    int64_t base[WS ? kKeyReaders : 1];
+    int64_t entry[kKeyReaders];
     int count[WS ? kKeyReaders : 1];
-    float fq[WS ? kKeyReaders : 1], ft[WS ? kKeyReaders : 1];
+    float alpha[WS ? kKeyReaders : 1], share[WS ? kKeyReaders : 1];
 };
 
-// Entries [r0, r0 + kKeyReaders) of the block's list, this thread's share
-// (its entries are numbered from `start` in the order of scan_key_readers).
+// Entries [r0, r0 + kKeyReaders) of the list, this thread's share (its
+// entries are numbered from `start` in the order of scan_key_readers).
 template <bool WS>
-__device__ __forceinline__ void fill_key_list(const PoseArgs &P, int C, int clip, int key, int start, int r0,
-                                              KeyList<WS> &L)
+__device__ __forceinline__ void fill_key_list(const PoseArgs &P, int C, int clip, int key, int nk, uint64_t &users,
+                                              int start, int r0, KeyList<WS> &L)
 {
     int idx = start;
     const int r1 = r0 + kKeyReaders;
-    scan_key_readers(P, C, clip, key, [&](int e, float alpha) {
+    scan_key_readers(P, C, clip, key, nk, users, true, [&](int64_t e, float alpha) {
         if (idx >= r0 && idx < r1) {
             const int i = idx - r0;
-            L.entry[i] = e;
             if constexpr (WS) {
-                const int c = e >> 2, X = (e >> 1) & 1, role = e & 1;
+                const int c = (int)(e >> 5);
                 const int64_t b = P.offsets[c];
-                L.base[i] = b;
-                L.count[i] = (int)(P.offsets[c + 1] - b);
+                const int n = (int)(P.offsets[c + 1] - b);
                 const float w = P.weight[c];
-                const float a = role == 0 ? 1.0f - alpha : alpha;
-                L.fq[i] = a;
-                L.ft[i] = a * (X ? w : 1.0f - w);
+                L.entry[i] = 32 * (n > 0 ? b : 0) + (e & 31);  // of an empty one: any row that exists
+                L.count[i] = n;
+                L.alpha[i] = alpha;
+                L.share[i] = e & 16 ? w : 1.0f - w;
+            } else {
+                L.entry[i] = e;
             }
         }
         ++idx;
     });
 }
 
-template <bool WS>
+// Adds one reader's terms to the keys it serves (t0, t1 as in key_entries,
+// uniform in the wave); s[k]: the arc sign between key k and the one before.
+template <int KEYS>
+__device__ __forceinline__ void add_reader(float4 gq[KEYS], float gt[KEYS][3], int t0, int t1, float alpha,
+                                           float share, const float s[KEYS], const float4 &vb, const float g[3])
+{
+#pragma unroll
+    for (int k = 0; k < KEYS; ++k) {
+        if (t0 == k + 1) {
+            const float u = 1.0f - alpha;
+            fma4(gq[k], u, vb);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) gt[k][i] = fmaf(u * share, g[i], gt[k][i]);
+        }
+        if (t1 == k + 1) {
+            fma4(gq[k], alpha * s[k], vb);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) gt[k][i] = fmaf(alpha * share, g[i], gt[k][i]);
+        }
+    }
+}
+
+template <bool WS, int KEYS>
 __global__ void __launch_bounds__(kSampleBwdThreads)
 sample_bwd_keys_kernel(PoseArgs P, SampleBwdArgs A)
 {
@@ -2789,12 +2846,15 @@ sample_bwd_keys_kernel(PoseArgs P, SampleBwdArgs A)
     __shared__ int wsum[kSampleBwdThreads / kWave];
     const int K = P.num_keys, J = P.joints_per_clip;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int64_t nblocks = (int64_t)P.num_clips * K;
+    const int groups = (K + KEYS - 1) / KEYS;  // of a clip's keys
+    const int64_t nblocks = (int64_t)P.num_clips * groups;
     for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        const int clip = (int)(blk / K), key = (int)(blk % K);
+        const int clip = (int)(blk / groups), key = KEYS * (int)(blk % groups), nk = min(KEYS, K - key);
+        const int64_t row0 = ((int64_t)clip * K + key) * J;
         // this thread's entries, then their place in the list
+        uint64_t users = 0;
         int mine = 0;
-        scan_key_readers(P, A.C, clip, key, [&](int, float) { ++mine; });
+        scan_key_readers(P, A.C, clip, key, nk, users, false, [&](int64_t, float) { ++mine; });
         int incl = mine;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -2809,75 +2869,115 @@ sample_bwd_keys_kernel(PoseArgs P, SampleBwdArgs A)
             if (w < wave) start += wsum[w];
             total += wsum[w];
         }
+        if (P.offsets[A.C] == 0) total = 0;    // no joint at all: nothing to add
         const bool once = total <= kKeyReaders;  // uniform in the workgroup
-        if (once) fill_key_list<WS>(P, A.C, clip, key, start, 0, L);
-        __syncthreads();
         for (int j0 = 0; j0 < J; j0 += kSampleBwdThreads) {
             const int j = j0 + (int)threadIdx.x;
-            float4 gkq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            float gkt[3] = {0.0f, 0.0f, 0.0f};
-            // a reader of this block as its k1 has k0 = key - 1: the arc sign
-            // of its clip blend depends on the two key rows alone (the same
-            // fp64 decision as the reverse step's)
-            float s1 = 1.0f;
-            if (WS && j < J) {
-                const float4 *kq = reinterpret_cast<const float4 *>(P.key_quat);
-                const float4 a = kq[((int64_t)clip * K + (key == 0 ? K - 1 : key - 1)) * J + j];
-                const float4 b = kq[((int64_t)clip * K + key) * J + j];
-                double d = (double)a.x * (double)b.x;
-                d = d + (double)a.y * (double)b.y;
-                d = d + (double)a.z * (double)b.z;
-                d = d + (double)a.w * (double)b.w;
-                s1 = d < 0.0 ? -1.0f : 1.0f;
+            float4 gq[KEYS];
+            float gt[KEYS][3], s[KEYS];
+            // a reader of key k as its k1 has k0 = k - 1: the arc sign of its
+            // clip blend depends on the two key rows alone (the same fp64
+            // decision as the reverse step's)
+            const float4 *kq = reinterpret_cast<const float4 *>(P.key_quat);
+#pragma unroll
+            for (int k = 0; k < KEYS; ++k) {
+                gq[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                gt[k][0] = gt[k][1] = gt[k][2] = 0.0f;
+                s[k] = 1.0f;
+                if (j < J && k < nk) {
+                    const float4 a = kq[((int64_t)clip * K + (key + k == 0 ? K - 1 : key + k - 1)) * J + j];
+                    const float4 b = kq[row0 + (int64_t)k * J + j];
+                    double d = (double)a.x * (double)b.x;
+                    d = d + (double)a.y * (double)b.y;
+                    d = d + (double)a.z * (double)b.z;
+                    d = d + (double)a.w * (double)b.w;
+                    s[k] = d < 0.0 ? -1.0f : 1.0f;
+                }
             }
             for (int r0 = 0; r0 < total; r0 += kKeyReaders) {
-                if (!once) {
-                    __syncthreads();  // the previous round's entries are read
-                    fill_key_list<WS>(P, A.C, clip, key, start, r0, L);
+                if (!once || j0 == 0) {  // uniform in the workgroup
+                    __syncthreads();     // the previous round's entries are read
+                    fill_key_list<WS>(P, A.C, clip, key, nk, users, start, r0, L);
                     __syncthreads();
                 }
-                const int nr = min(kKeyReaders, total - r0);
-                for (int e = 0; e < nr; ++e) {
-                    const int ent = L.entry[e];
-                    const int X = (ent >> 1) & 1, role = ent & 1;
-                    if constexpr (WS) {
-                        // the reader's reverse step, stored by the time/weight kernel
-                        if (j >= L.count[e]) continue;  // the character has no joint j
-                        const int64_t g = L.base[e] + j;
-                        const float4 vb = A.ws[2 * g + X];
-                        const float f = role == 0 ? L.fq[e] : L.fq[e] * s1;
-                        const float ft = L.ft[e];
-                        fma4(gkq, f, vb);
+                const int nr = __builtin_amdgcn_readfirstlane(min(kKeyReaders, total - r0));
+                if constexpr (WS) {
+                    // the readers' reverse steps, stored by the time/weight
+                    // kernel: 64 entries are read from the list at a time,
+                    // one a lane, and handed to scalar registers, so that a
+                    // row in flight costs its own seven registers; the rows
+                    // are added in the list's order
+                    for (int e0 = 0; e0 < nr; e0 += kWave) {
+                        const int m = min(kWave, nr - e0);
+                        const int i = e0 + min(lane, m - 1);
+                        const int64_t ent = L.entry[i];
+                        const int el = (int)ent, eh = (int)(ent >> 32), cnt = L.count[i];
+                        const int al = __float_as_int(L.alpha[i]), shr = __float_as_int(L.share[i]);
+                        for (int e = 0; e < m; e += kKeyAhead) {
+                            bool in[kKeyAhead];
+                            float4 vb[kKeyAhead];
+                            float g[kKeyAhead][3];
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) gkt[i] = fmaf(ft, A.grad_trans[3 * g + i], gkt[i]);
-                    } else {
-                        const int rc = ent >> 2;
-                        const int64_t base = P.offsets[rc];
-                        if (j >= (int)(P.offsets[rc + 1] - base)) continue;  // the character has no joint j
+                            for (int k = 0; k < kKeyAhead; ++k) {
+                                const int x = min(e + k, m - 1);
+                                const int lo = __builtin_amdgcn_readlane(el, x);
+                                const int64_t base =
+                                    (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(eh, x) << 32) | (uint32_t)lo) >> 5;
+                                // a thread past the list, or past the character's
+                                // joints, reads a row of the list's and drops it
+                                const int left = __builtin_amdgcn_readlane(cnt, x) - j0;
+                                in[k] = e + k < m && (int)threadIdx.x < left;
+                                const int64_t b = base + (left > 0 ? j0 : 0);
+                                const uint32_t t = min((uint32_t)threadIdx.x, (uint32_t)max(left - 1, 0));
+                                vb[k] = (A.ws + 2 * b + (lo >> 4 & 1))[2 * t];
+#pragma unroll
+                                for (int i2 = 0; i2 < 3; ++i2) g[k][i2] = (A.grad_trans + 3 * b)[3 * t + i2];
+                            }
+                            __builtin_amdgcn_sched_barrier(0);  // all loads before the first wait
+#pragma unroll
+                            for (int k = 0; k < kKeyAhead; ++k) {
+                                const int x = min(e + k, m - 1);
+                                const int lo = __builtin_amdgcn_readlane(el, x);
+                                const float alpha = __int_as_float(__builtin_amdgcn_readlane(al, x));
+                                const float share = __int_as_float(__builtin_amdgcn_readlane(shr, x));
+                                if (in[k]) add_reader<KEYS>(gq, gt, lo & 3, lo >> 2 & 3, alpha, share, s, vb[k], g[k]);
+                            }
+                        }
+                    }
+                } else {
+                    for (int e = 0; e < nr; ++e) {
+                        const int64_t ent = L.entry[e];
+                        const int lo = __builtin_amdgcn_readfirstlane((int)ent);
+                        const int c = __builtin_amdgcn_readfirstlane((int)(ent >> 5));
+                        const int64_t base = P.offsets[c];
+                        if (j >= (int)(P.offsets[c + 1] - base)) continue;  // the character has no joint j
                         int k0, k1;
                         float alpha;
-                        sample_frame(P, rc, k0, k1, alpha);
-                        const int cl[2] = {P.clip_a[rc], P.clip_b[rc]};
+                        sample_frame(P, c, k0, k1, alpha);
+                        const int cl[2] = {P.clip_a[c], P.clip_b[c]};
+                        const float w = P.weight[c];
                         JointRev o;
-                        joint_reverse(P, A, base + j, j, cl, k0, k1, alpha, P.weight[rc], o);
-                        // X is only known at run time: select, not index (no scratch)
-                        const float4 vb = X ? o.vb[1] : o.vb[0];
-                        const float sx = X ? o.sX[1] : o.sX[0], tw = X ? o.tw[1] : o.tw[0];
-                        const float f = role == 0 ? 1.0f - alpha : alpha * sx;
-                        const float ft = (role == 0 ? 1.0f - alpha : alpha) * tw;
-                        fma4(gkq, f, vb);
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) gkt[i] = fmaf(ft, o.gt[i], gkt[i]);
+                        joint_reverse(P, A, base + j, j, cl, k0, k1, alpha, w, o);
+                        const bool X = lo >> 4 & 1;
+                        // X is only known at run time: select the values, not
+                        // the element (no scratch)
+                        const float4 vb = make_float4(X ? o.vb[1].x : o.vb[0].x, X ? o.vb[1].y : o.vb[0].y,
+                                                      X ? o.vb[1].z : o.vb[0].z, X ? o.vb[1].w : o.vb[0].w);
+                        add_reader<KEYS>(gq, gt, lo & 3, lo >> 2 & 3, alpha, X ? w : 1.0f - w, s, vb, o.gt);
                     }
                 }
             }
             if (j < J) {
-                const int64_t row = blk * J + j;
-                if (A.grad_key_quat) reinterpret_cast<float4 *>(A.grad_key_quat)[row] = gkq;
-                if (A.grad_key_trans) {
-                    A.grad_key_trans[3 * row] = gkt[0];
-                    A.grad_key_trans[3 * row + 1] = gkt[1];
-                    A.grad_key_trans[3 * row + 2] = gkt[2];
+#pragma unroll
+                for (int k = 0; k < KEYS; ++k) {
+                    if (k >= nk) break;
+                    const int64_t row = row0 + (int64_t)k * J + j;
+                    if (A.grad_key_quat) reinterpret_cast<float4 *>(A.grad_key_quat)[row] = gq[k];
+                    if (A.grad_key_trans) {
+                        A.grad_key_trans[3 * row] = gt[k][0];
+                        A.grad_key_trans[3 * row + 1] = gt[k][1];
+                        A.grad_key_trans[3 * row + 2] = gt[k][2];
+                    }
                 }
             }
         }
@@ -4495,12 +4595,17 @@ hipError_t launch_pose_sample_backward(const PoseArgs &pose, const SampleBwdArgs
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if (keys) {
-        const int64_t blocks = (int64_t)pose.num_clips * pose.num_keys;
-        const dim3 grid((unsigned)std::min<int64_t>(blocks, 1 << 20));
-        if (a.ws)
-            hipLaunchKernelGGL(sample_bwd_keys_kernel<true>, grid, dim3(kSampleBwdThreads), 0, stream, pose, a);
-        else
-            hipLaunchKernelGGL(sample_bwd_keys_kernel<false>, grid, dim3(kSampleBwdThreads), 0, stream, pose, a);
+        // two keys a workgroup where that leaves one for each of 256 CUs
+        // (whole gradient of the sampler and the scan, two keys against one:
+        // 64 clips of 30 keys 304 against 319 us, 30 clips 167 against 176,
+        // 16 clips 183 either way, 2 clips 442 against 313)
+        const int64_t pairs = (int64_t)pose.num_clips * ((pose.num_keys + 1) / 2);
+        const bool two = pairs >= 256;
+        const int64_t blocks = two ? pairs : (int64_t)pose.num_clips * pose.num_keys;
+        const auto kern = a.ws ? (two ? sample_bwd_keys_kernel<true, 2> : sample_bwd_keys_kernel<true, 1>)
+                               : (two ? sample_bwd_keys_kernel<false, 2> : sample_bwd_keys_kernel<false, 1>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min<int64_t>(blocks, 1 << 20)), dim3(kSampleBwdThreads), 0, stream,
+                           pose, a);
         err = hipGetLastError();
     }
     return err;
