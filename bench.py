@@ -87,12 +87,15 @@ BYTES_PER_JOINT = {
     # (+ 12 B of targets per effector)
     "differentiable": 136,
 }
-DOMINANT = {"differentiable": "bwd_anchor_kernel",
+DOMINANT = {"differentiable": "bwd_path_kernel",
             "long_chains": "mp_chain_kernel (one-pass multipass for chains)"}
+# the dense route's adjoint, by --adjoint
+DENSE_KERNEL = {"auto": "bwd_path_kernel", "rounds": "bwd_sync_kernel", "dataflow": "bwd_tile_kernel",
+                "anchors": "bwd_anchor_kernel"}
 # what a --pmc dispatch's kernel name must contain to be the dominant
 # kernel: the differentiable run also times the dense route, whose adjoint
-# is the other instance of the same template
-PMC_MATCH = {"differentiable": ("bwd_anchor_kernel<", ", 2>")}
+# is another instance of the same template (the last argument: the seed)
+PMC_MATCH = {"differentiable": (", 2>",)}
 # fused workloads: the instance that samples poses in the kernel
 SAMPLE_INSTANCE = ", true"
 # steps of several kernels: HBM traffic per step is the sum over them
@@ -179,9 +182,13 @@ def summarize_pmc(workload, fetch_csv, write_csv):
         with open(fetch_csv) as f:
             queued = any("fwd_queue_kernel" in r.get("Kernel_Name", "") for r in csv.DictReader(f))
         kname = "fwd_queue_kernel" if queued else "fwd_tile_kernel"
+    elif workload == "differentiable":
+        with open(fetch_csv) as f:
+            if not any(kname in r.get("Kernel_Name", "") for r in csv.DictReader(f)):
+                kname = "bwd_anchor_kernel"  # --adjoint anchors
     # a step of several kernels (the multipass path) sums their averages
-    parts = STEP_KERNELS.get(workload) or [PMC_MATCH.get(workload, (kname,) + ((SAMPLE_INSTANCE,) if workload in FUSED
-                                                                             else ()))]
+    parts = STEP_KERNELS.get(workload) or [(kname,) + PMC_MATCH.get(workload, (SAMPLE_INSTANCE,) if workload in FUSED
+                                                                    else ())]
 
     def per_kernel(path, counter):
         scan, copy = [[] for _ in parts], None
@@ -556,6 +563,8 @@ def measure(args, name):
                             else "fwd_tile_kernel")
     if diff and args.adjoint in ("rounds", "dataflow"):
         dominant = "bwd_sync_kernel"  # the effector step's kernel under these options
+    elif diff and args.adjoint == "anchors":
+        dominant = "bwd_anchor_kernel"
     # one launch per step (the forward's work queue or classes launched back
     # to back; the differentiable step's one kernel): HIP events around the
     # timed region give the step's mean kernel time, on the cycled sets
@@ -604,7 +613,7 @@ def measure(args, name):
         "launch_modes": launch,
     }
     if diff:
-        out["memory_modes"] = memory_modes(w)
+        out["memory_modes"] = memory_modes(w, args.adjoint)
     if name == "heterogeneous" and not args.no_schedules and not args.calibrate_copy:
         out["schedules"] = schedule_alternatives(w, info)
     if not args.no_cpu_baseline:
@@ -655,7 +664,7 @@ def schedule_alternatives(w, info, steps=60, warmup=10):
     return res
 
 
-def memory_modes(w):
+def memory_modes(w, adjoint):
     """The differentiable form through the general adjoint (dense
     dLoss/dG) in its two memory modes: the whole step per mode (captured,
     CKPT_K-step graphs) and the adjoint launch alone, with the adjoint's
@@ -674,7 +683,7 @@ def memory_modes(w):
         adj = w.adjoint_ms(ck)
         nbytes = N * 136 + ((N * 4 + n_ck * 48) if ck else 0)
         res[key] = {"ms_per_step": step, "adjoint_kernel": "bwd_tile_kernel (checkpoints)" if ck else
-                    "bwd_sync_kernel (dense seed)", "adjoint_kernel_ms": adj,
+                    DENSE_KERNEL[adjoint] + " (dense seed)", "adjoint_kernel_ms": adj,
                     "adjoint_algorithmic_bytes": nbytes,
                     "adjoint_frac": nbytes / (adj * 1e-3) / 1e9 / HBM_PEAK_GBS,
                     "checkpointed_joints": n_ck if ck else 0}

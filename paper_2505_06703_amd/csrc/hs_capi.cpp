@@ -164,7 +164,7 @@ hipError_t fetch(std::vector<T> &dst, const T *src, size_t n)
 
 // f(begin, end) over pieces of [0, n), on up to eight threads, one for every
 // 16 384 joints of `work`: about the time that starting a thread takes (plans
-// of 220 000 and 1 000 000 joints of unlike skeletons: 4.2 and 10 ms, against
+// of 210 000 and 590 000 joints of unlike skeletons: 4.2 and 10 ms, against
 // 8.2 and 16 with one for every 262 144).  The pieces are independent; what a piece
 // throws is thrown again here, and if no thread can be started the calling
 // one does everything.
