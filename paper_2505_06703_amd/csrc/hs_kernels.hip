@@ -1774,10 +1774,10 @@ bwd_sync_kernel(TileLaunch tl, PoseArgs pose, BwdArgs bwd)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool any_nonzero12(const float v[12])
 {
-    bool nz = false;
+    uint32_t bits = 0;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) nz |= v[k] != 0.0f;
-    return nz;
+    for (int k = 0; k < 12; ++k) bits |= __float_as_uint(v[k]);
+    return bits << 1 != 0;  // the signs dropped
 }
 
 // In-wave reverse pointer jumping over the block's in-block parents: S holds
@@ -2241,7 +2241,9 @@ __device__ __forceinline__ void path_rounds(float M[12], float S[12], int a, int
 }
 
 template <int WAVES, int SEED>
-__global__ void __launch_bounds__(WAVES * kWave, 3)  // at most 168 VGPRs: three waves per SIMD
+// at most 168 VGPRs, three waves a SIMD; with seeds from a given forward 128
+// do, for four (4000 x 512 joints: 66 us against 80 with three)
+__global__ void __launch_bounds__(WAVES * kWave, SEED == kSeedEffectors ? 4 : 3)
 bwd_path_kernel(PathLaunch pl, PoseArgs pose, BwdArgs bwd)
 {
     constexpr int K = kPathLen;
@@ -2386,6 +2388,7 @@ bwd_path_kernel(PathLaunch pl, PoseArgs pose, BwdArgs bwd)
                         const float *g = bwd.eff_global + 16 * bwd.eff_ids[e];
 #pragma unroll
                         for (int r = 0; r < 3; ++r) X[k][4 * r + 3] = 2.0f * (g[4 * r + 3] - y[r]);
+                        any = X[k][3] != 0.0f || X[k][7] != 0.0f || X[k][11] != 0.0f;
                     }
                 }
                 if (any) adj_pull_add(X[k], Q, W);
@@ -2468,7 +2471,9 @@ bwd_path_kernel(PathLaunch pl, PoseArgs pose, BwdArgs bwd)
 #pragma unroll
                     for (int c = 0; c < 12; ++c) X[k][c] += in[c];
                 }
-                if (k > 0) adj_pull_add(X[k], L[k], X[k > 0 ? k - 1 : 0]);
+                // with no seed below it a joint sends nothing, also where its
+                // transform is not finite
+                if (k > 0 && (!SPARSE || any_nonzero12(X[k]))) adj_pull_add(X[k], L[k], X[k > 0 ? k - 1 : 0]);
             }
         }
     }
