@@ -518,6 +518,7 @@ struct hs_plan {
     int32_t *d_bcode = nullptr;  // anchor codes of the adjoint tiles' joints
     int32_t b_max_anchors = 0;
     bool b_anchor_ok = false;    // the two-level adjoint fits the LDS
+    int key_cap = 0;             // the capacity whose block chains name the batch in a tuning cache
     int b_bpw_opt = 0;           // the two-level adjoint's blocks per wave as asked (0 = choose)
     int b_bpw[3] = {1, 1, 1};    // ... as chosen, per seed kind (dense, effectors, forward in the tile)
     bool b_one_round[3] = {false, false, false};  // with one block per wave every tile is resident at once
@@ -1811,12 +1812,19 @@ std::string tune_key(const hs_plan *p, int strategy)
 {
     // size class: number of joints (log2), largest character and deepest
     // block chain, rounded so that similar batches share an entry; the
-    // strategy and the instancing decide which candidates are allowed
+    // strategy and the instancing decide which candidates are allowed.  The
+    // block chains are those on tiles of key_cap joints: where characters
+    // start in a tile depends on its size.
+    int chain = p->info.max_block_chain;
+    if (p->key_cap > p->shape.tile_cap) {
+        const Packing pk = pack_tiles(p, p->key_cap, strategy, false);
+        chain = std::max(pk.max_chain_tiles, pk.max_chain_mp);
+    }
     char buf[160];
     snprintf(buf, sizeof buf, "%s|N%d|maxc%d|chain%d|chars%d|inst%d|strat%d|sched%d", p->ctx->arch.c_str(),
              ceil_log2(std::max<int64_t>(1, p->N)), round_up(std::max(1, p->info.max_character), 64),
-             ceil_log2(std::max(1, p->info.max_block_chain)), ceil_log2(std::max<int64_t>(1, p->C)),
-             p->inst ? 1 : 0, strategy, p->sched_opt);
+             ceil_log2(std::max(1, chain)), ceil_log2(std::max<int64_t>(1, p->C)), p->inst ? 1 : 0, strategy,
+             p->sched_opt);
     return buf;
 }
 
@@ -2249,6 +2257,7 @@ hs_status create_plan(hs_context *ctx, const hs_batch *batch, const hs_plan_opts
     } else {
         const int64_t target = (N + 2 * (int64_t)ctx->num_cu - 1) / (2 * (int64_t)ctx->num_cu);
         sh.tile_cap = (int)std::min<int64_t>(1024, round_up((int)std::max<int64_t>(64, target), 64));
+        plan->key_cap = sh.tile_cap;  // not the narrower one below: caches written before it stay valid
         // no larger than the largest character needs, from 256 joints on: small
         // workgroups, several of them on a CU at a time, overlap their phases
         // (10 000 x 256 joints, scan and skinning in one pass: 102 us on
