@@ -178,11 +178,14 @@ typedef struct hs_plan_opts {
  * fit the LDS fall back to HS_ADJ_ROUNDS).  HS_ADJ_AUTO resolves per call:
  * the path adjoint -- every tree cut into pieces of paths, one piece per
  * thread, pointer jumping over the pieces only; it has no bounded waits --
- * for a dense dLoss/dG, and for end-effector seeds once the tiles of
- * HS_ADJ_ANCHORS would not all be resident at once (HS_ADJ_ANCHORS until
- * then); where the path adjoint does not apply (a character of more than
- * 512 pieces, more than 64 pieces below one joint, or a wait limit of zero)
- * HS_ADJ_ANCHORS for end-effector seeds and HS_ADJ_ROUNDS for a dense
+ * where the plan expects it to be the quicker: for a dense dLoss/dG on most
+ * batches (not on a few tiles of trees with little to jump over or many
+ * pieces below one, nor on chains of up to 32 joints), for end-effector seeds
+ * once the tiles of HS_ADJ_ANCHORS would not all be resident at once (and
+ * not on trees whose pieces are mostly single joints); elsewhere, and where
+ * the path adjoint does not apply (a character of more than 512 pieces, more
+ * than 64 pieces below one joint, or a wait limit of zero), HS_ADJ_ANCHORS
+ * for end-effector seeds and HS_ADJ_ROUNDS for a dense
  * dLoss/dG.  Given checkpoints, characters of up
  * to 1664 joints always run the dataflow kernel, which rebuilds each G_j
  * from them. */

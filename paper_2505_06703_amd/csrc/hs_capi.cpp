@@ -522,10 +522,12 @@ struct hs_plan {
     int b_bpw_opt = 0;           // the two-level adjoint's blocks per wave as asked (0 = choose)
     int b_bpw[3] = {1, 1, 1};    // ... as chosen, per seed kind (dense, effectors, forward in the tile)
     bool b_one_round[3] = {false, false, false};  // with one block per wave every tile is resident at once
+    int64_t b_rounds[3] = {0, 0, 0};              // rounds of resident workgroups, with b_bpw
     int64_t bwd_untiled = 0;  // joints the adjoint's tiles do not cover
-    // the path adjoint over the same characters as d_btiles (num_tiles = 0:
-    // the plan asked for another kernel, or the characters do not suit it)
+    // the path adjoint over the same characters as d_btiles (no tiles: the
+    // plan asked for another kernel, or the characters do not suit it)
     struct PathSet {
+        bool use[3] = {false, false, false};  // takes seeds of this kind (dense, effectors, forward in the tile)
         char *d_tables = nullptr;  // one allocation: tiles, lanes, steps, slots
         const hs::PathTile *d_tiles = nullptr;
         const hs::PathLane *d_lanes = nullptr;
@@ -1119,8 +1121,11 @@ std::vector<int> all_tile_codes(const hs_plan *plan, const std::vector<TileDesc>
 // The pieces of one character (parents pa, n joints): each joint's piece,
 // counted from 0, and its place in it.  Returns their number, or -1 when too
 // many lie below one joint.
-int cut_paths(const int32_t *pa, int64_t n, int16_t *lane, uint8_t *pos, std::vector<int16_t> &height,
-              std::vector<int16_t> &best, std::vector<int16_t> &fan)
+// `losers`: the sends of the synchronous rounds that find their receiver taken.
+// Round r has a sender for each joint at least 2^r levels below the top and a
+// receiver for each at least 2^r above the lowest joint below it.
+int cut_paths(const int32_t *pa, const int32_t *level, int64_t n, int16_t *lane, uint8_t *pos,
+              std::vector<int16_t> &height, std::vector<int16_t> &best, std::vector<int16_t> &fan, int32_t &losers)
 {
     height.assign((size_t)n, 1);
     best.assign((size_t)n, -1);
@@ -1140,13 +1145,17 @@ int cut_paths(const int32_t *pa, int64_t n, int16_t *lane, uint8_t *pos, std::ve
         lane[j] = at == 0 ? (int16_t)pieces++ : lane[p];
         if (at == 0 && p >= 0 && ++fan[p] > hs::kPathMaxFanIn) return -1;
     }
+    auto rounds = [](int levels) { return levels > 0 ? 32 - __builtin_clz((unsigned)levels) : 0; };
+    losers = 0;
+    for (int64_t j = 0; j < n; ++j) losers += rounds(level[j] - 1) - rounds(height[j] - 1);
     return pieces;
 }
 
 // One tile's tables: characters c .. e - 1 (t.begin, count and lanes are
 // set); slot and pl: its joints' rows and its lanes.  The step words go to
-// `steps`.
-void fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e, const std::vector<int32_t> &pieces,
+// `steps`.  Returns the time in us that one such tile spends on jumping and on
+// rows added one after the other (choose_paths).
+double fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e, const std::vector<int32_t> &pieces,
                     const int16_t *lane, const uint8_t *pos, uint16_t *slot, hs::PathLane *pl,
                     std::vector<uint32_t> &steps)
 {
@@ -1223,6 +1232,9 @@ void fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e, 
     // the rounds' rows: the senders sorted by branch in the first one, by the
     // lane they reach in the others
     std::vector<int> next(nl), first, count(nl), row_of(nl);
+    int longest = 0, most_kids = 0;  // rows that the busiest lanes add, round by round; below one joint
+    for (size_t l = 0; l < nl; ++l)
+        for (int k = 0; k < K; ++k) most_kids = std::max(most_kids, (int)(pl[l].kids >> 8 * k & 0xff));
     for (int r = 0; r < t.rounds; ++r) {
         first.assign(nl + 1, 0);
         std::fill(count.begin(), count.end(), 0);
@@ -1231,6 +1243,7 @@ void fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e, 
                 ++count[up[l]];
                 ++first[(r == 0 ? pl[l].from - 1 : up[l]) + 1];
             }
+        longest += *std::max_element(count.begin(), count.end());
         for (size_t i = 0; i < nl; ++i) first[i + 1] += first[i];
         for (size_t l = 0; l < nl; ++l) row_of[l] = up[l] >= 0 ? first[r == 0 ? pl[l].from - 1 : up[l]]++ : 0;
         for (size_t l = 0, sum = 0; l < nl; sum += count[l++])
@@ -1238,6 +1251,69 @@ void fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e, 
         for (size_t l = 0; l < nl; ++l) next[l] = up[l] >= 0 ? up[up[l]] : -1;
         up.swap(next);
     }
+    return 1.1 * t.rounds + 0.06 * longest + 0.05 * most_kids;
+}
+
+// Which seeds the path adjoint serves.  It has a third of the other kernels'
+// work on trees of long paths, but a tile takes it longer where there is little
+// to jump over, or many pieces below one, and a piece of one joint costs a
+// thread all the same.  Fitted to 270 batches of chains, random trees, k-ary
+// trees, stars and humanoids of 5 to 1000 joints, 5 to 2 000 000 in all.
+//
+// Dense seeds: with more than four tiles of the synchronous rounds for each CU
+// the path adjoint (10 000 x 256 joints: 96 against 170 us), except on chains
+// of at most 32 joints, whose rounds never contend (125 000 x 16: 65 against
+// 52 us).  With fewer, one tile's latency counts, and the lower of two
+// estimates in us decides.  The rounds': R rounds of w waves, and sends to a
+// receiver that is taken, LDS atomics one after the other for all tiles of a
+// CU.  The path adjoint's: what fill_path_tile returned, and its waves.  Both
+// are within 15 % of the measured times mostly, and so is the call of the better
+// kernel's (64 x 1000-joint trees: paths 20 against 57 us; 1000 stars of 60: 17
+// against 9; 200 humanoids of 256 joints: 12.7 against 10.7).
+//
+// End-effector seeds: the two-level kernel while all its tiles are resident
+// at once (200 x 512 joints: 16.3 against 18.3 us), and beyond that where the
+// path adjoint needs too many threads for a joint: more than 0.6 for the step,
+// which jumps twice (k-ary trees of 250 joints and arity 2, 3, 8, one thread a
+// joint: 160, 182, 214 against 123, 100, 87 us; humanoids of 256 joints, a third
+// of one: 84 against 104), more than 0.8 for the adjoint of a given forward if
+// the estimates say so too (the same trees: 100, 112, 134 against 118, 93, 78 us).
+void choose_paths(hs_plan *plan, const std::vector<double> &jump, const std::vector<int32_t> &losers, size_t tiles)
+{
+    auto &P = plan->paths;
+    const int64_t nc = std::max(1, plan->ctx->num_cu);
+    auto rounds_of = [&](int64_t n, int64_t per_cu) { return (double)((n + per_cu * nc - 1) / (per_cu * nc)); };
+    int64_t joints = 0, contended = 0;
+    int R = 0;
+    for (const TileDesc &t : plan->h_btiles) {
+        int64_t sum = 0;
+        for (int32_t c = t.first_char; c < t.first_char + t.num_chars; ++c) sum += losers[c];
+        contended = std::max(contended, sum);
+        joints += t.count;
+        R = std::max(R, t.rounds);
+    }
+    const int64_t st = (int64_t)plan->h_btiles.size();
+    const double per_cu = rounds_of(st, 1), more = std::max(0.0, (double)joints / (256.0 * (double)nc) - 1.0);
+    int w = 1;
+    while (w * 64 < plan->bwd_cap) w *= 2;
+    const int64_t s_occ = std::max<int64_t>(
+        1, std::min<int64_t>(16 / w, (int64_t)(plan->ctx->max_lds / hs::backward_sync_lds_bytes(plan->bwd_cap))));
+    const double t_rounds = 3.5 + 0.2 * R + 0.085 * R * w * rounds_of(st, s_occ) +
+                            0.0175 * (double)contended * per_cu + 1.7 * more;
+    const int pw = P.threads / 64;
+    auto resident = [&](int waves) {  // a workgroup's waves spread over the four SIMDs
+        return rounds_of((int64_t)tiles, pw < 4 ? 4 * waves / pw : std::max(1, waves / ((pw + 3) / 4)));
+    };
+    const double most = *std::max_element(jump.begin(), jump.end());
+    const double t_paths = resident(3) * (4.3 + most + 0.6 * pw) + 1.2 * more;
+    P.use[0] = !(contended == 0 && R <= 5) && (per_cu > 4.0 || t_paths < t_rounds);
+    // threads for a joint, those of idle SIMD slots counted
+    const double threads = (double)tiles * (pw <= 4 ? P.threads : round_up(P.threads, 256)) / (double)joints;
+    const double t_given = resident(4) * (5.4 + 0.9 * most) + 0.9 * more;
+    const double t_anchors = (double)plan->b_rounds[1] * (6.2 + 0.5 * R + 0.6 * w + 0.02 * plan->b_max_anchors +
+                                                          4.3 * (plan->b_bpw[1] - 1)) + 0.7 * more;
+    P.use[1] = !plan->b_anchor_ok || (!plan->b_one_round[1] && (threads <= 0.8 || t_given < t_anchors));
+    P.use[2] = !plan->b_anchor_ok || (!plan->b_one_round[2] && threads <= 0.6);
 }
 
 hs_status build_paths(hs_plan *plan)
@@ -1250,14 +1326,15 @@ hs_status build_paths(hs_plan *plan)
     if (plan->num_btiles == 0) return HS_OK;  // no character of that size
     std::vector<int16_t> lane((size_t)N);  // piece of each joint, counted in its character
     std::vector<uint8_t> pos((size_t)N);   // place in the piece
-    std::vector<int32_t> pieces((size_t)C, 0);
+    std::vector<int32_t> pieces((size_t)C, 0), losers((size_t)C, 0);
     std::atomic<bool> fits{true};
     parallel_pieces(C, N, [&](int64_t b, int64_t e) {
         std::vector<int16_t> height, best, fan;
         for (int64_t c = b; c < e && fits; ++c) {
             const int64_t o = off[c], n = off[c + 1] - o;
             if (n == 0 || n > hs::kMaxSyncTileJoints) continue;
-            pieces[c] = cut_paths(plan->h_parents.data() + o, n, lane.data() + o, pos.data() + o, height, best, fan);
+            pieces[c] = cut_paths(plan->h_parents.data() + o, plan->h_level.data() + o, n, lane.data() + o,
+                                  pos.data() + o, height, best, fan, losers[c]);
             if (pieces[c] < 0 || pieces[c] > hs::kPathMaxLanes) fits = false;
         }
     });
@@ -1339,13 +1416,17 @@ hs_status build_paths(hs_plan *plan)
     std::vector<hs::PathLane> lanes((size_t)used_lanes);
     std::vector<uint16_t> slot((size_t)used_slots);
     std::vector<std::vector<uint32_t>> tile_steps(nt);
+    std::vector<double> jump(nt, 0.0);
     parallel_pieces((int64_t)own.size(), used_slots, [&](int64_t b, int64_t e) {
         for (int64_t k = b; k < e; ++k) {
             const size_t i = own[k];
-            fill_path_tile(plan, tiles[i], chars[i].first, chars[i].second, pieces, lane.data(), pos.data(),
-                           slot.data() + tiles[i].slot_begin, lanes.data() + tiles[i].lane_begin, tile_steps[i]);
+            jump[i] = fill_path_tile(plan, tiles[i], chars[i].first, chars[i].second, pieces, lane.data(), pos.data(),
+                                     slot.data() + tiles[i].slot_begin, lanes.data() + tiles[i].lane_begin,
+                                     tile_steps[i]);
         }
     });
+    choose_paths(plan, jump, losers, nt);
+    if (!P.use[0] && !P.use[1] && !P.use[2]) return HS_OK;
     size_t words = 0;
     for (size_t i : own) words += tile_steps[i].size();
     std::vector<uint32_t> steps(words);
@@ -1557,6 +1638,7 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
                 if (bpw == 1 && occ1 == 0) plan->b_anchor_ok = false;
                 plan->b_bpw[kind] = bpw;
                 plan->b_one_round[kind] = r1 == 1;
+                plan->b_rounds[kind] = bpw == 2 ? r2 : r1;
             }
         }
         plan->num_bbig = (int32_t)pb.tiles.size();
@@ -2711,17 +2793,10 @@ hs_status run_backward(const hs_plan *plan, const hs::PoseArgs &pa, const hs::Bw
     tl.chain_units = 0;
     hipError_t err = hipSuccess;
     const int kind = ba.eff_ids ? (ba.eff_forward ? 2 : 1) : 0;
-    // The path adjoint does a third of the others' work, but one tile takes it
-    // longer than the two-level kernel with a wave for every block.  So while
-    // every tile of the latter is resident at once it serves end-effector seeds
-    // (steps of 512 x 512 joints: 21.3 against 22.0 us, 200 x 512: 16.3 against
-    // 18.3), the path adjoint beyond (640 x 512: 23.9 against 28.2, 1024 x 512:
-    // 26.5 against 33.7) and always for dense seeds (2048 characters of 32 to
-    // 1024 joints: 54 against 118 us in the synchronous rounds, 10 000 x 256
-    // joints: 96 against 170).  It has no bounded waits: a plan whose waits are
-    // to give up at once (a limit of zero polls) runs the kernels that wait.
-    const bool paths = !plan->paths.h_tiles.empty() && !ba.ckpt && plan->spin_limit > 0 &&
-                       (kind == 0 || !plan->b_anchor_ok || !plan->b_one_round[kind]);
+    // The path adjoint where the plan chose it (choose_paths).  It has no
+    // bounded waits: a plan whose waits are to give up at once (a limit of zero
+    // polls) runs the kernels that wait.
+    const bool paths = !plan->paths.h_tiles.empty() && plan->paths.use[kind] && !ba.ckpt && plan->spin_limit > 0;
     if (paths) {
         hs::BwdArgs pb = ba;
         if (ba.eff_ids) pb.eff_tile = eff_path_tile;
@@ -3035,7 +3110,8 @@ hs_status hs_effectors_create(const hs_plan *plan, int64_t num_effectors, const 
         };
         std::vector<int32_t> tile, ptile;
         int64_t covered = ranges(plan->h_btiles, tile);
-        if (!plan->paths.h_tiles.empty()) covered = std::min(covered, ranges(plan->paths.h_tiles, ptile));
+        if (!plan->paths.h_tiles.empty() && (plan->paths.use[1] || plan->paths.use[2]))
+            covered = std::min(covered, ranges(plan->paths.h_tiles, ptile));
         if (covered != E) {  // the adjoint's tiles cover every joint of such a plan
             free_effectors(e);
             return fail(HS_ERR_DEVICE, "hs_effectors_create: %lld ids outside the adjoint's tiles",
