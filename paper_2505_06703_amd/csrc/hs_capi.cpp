@@ -789,7 +789,7 @@ Packing pack_tiles(const hs_plan *plan, int cap, int strategy, bool chain_units,
 // e values, janc(c) is the index of e(c) among them, and the anchor-level
 // rounds cover the longest anchor chain.
 void build_anchors(const hs_plan *plan, const Packing &pk, std::vector<int32_t> &janc,
-                   std::vector<int32_t> &anchors, int &rounds)
+                   std::vector<int32_t> &anchors, int &levels)
 {
     const auto &gpar = plan->h_gparent;
     const int64_t nb = (int64_t)pk.mpb.size();
@@ -829,13 +829,27 @@ void build_anchors(const hs_plan *plan, const Packing &pk, std::vector<int32_t> 
         depth[i] = j < 0 ? 1 : depth[j] + 1;
         maxd = std::max(maxd, depth[i]);
     }
-    rounds = ceil_log2(maxd);
+    levels = maxd;
+}
+
+// More than one anchor in eight shares the anchor that it points to.
+bool branched(const std::vector<int32_t> &janc, const std::vector<int32_t> &anchors)
+{
+    std::vector<bool> taken(anchors.size(), false);
+    size_t shared = 0;
+    for (int32_t a : anchors) {
+        const int32_t up = janc[a];
+        if (up < 0) continue;
+        shared += taken[up];
+        taken[up] = true;
+    }
+    return shared * 8 > anchors.size();
 }
 
 // Sort each character's anchors by level, those of one level by their own
 // anchor (renumbers janc and anchors), and cut the list into trees, one per
 // character: false, with nothing changed, when some tree is too large for one
-// workgroup's LDS or deeper than level by level pays.
+// workgroup's LDS.
 bool plant_trees(const Packing &pk, std::vector<int32_t> &janc, std::vector<int32_t> &anchors,
                  std::vector<hs::MPTree> &trees, std::vector<int32_t> &lev, std::vector<int2> &kids)
 {
@@ -863,7 +877,7 @@ bool plant_trees(const Packing &pk, std::vector<int32_t> &janc, std::vector<int3
         int levels = 0;
         for (; i < na && anchors[i] < end; ++i) levels = std::max(levels, depth[i] + 1);
         if (i == begin) continue;
-        if (i - begin > (size_t)hs::kTreeMaxAnchors || levels > hs::kTreeMaxLevels) return false;
+        if (i - begin > (size_t)hs::kTreeMaxAnchors) return false;
         trees.push_back({(int32_t)begin, (int32_t)(i - begin), (int32_t)lev.size(), levels});
         // breadth first: the roots, then what lies below each in turn
         size_t at = begin;
@@ -944,7 +958,84 @@ hs_status make_chains(MPSet &m, const hs_plan *plan, const Packing &pk)
     return HS_OK;
 }
 
-hs_status make_mpset(MPSet &m, const hs_plan *plan, const Packing &pk, bool adjoint)
+// The anchors of a packing's multipass characters, and how the passes over
+// them run: in segments, level by level, or (neither) in rounds over all.
+struct Anchors {
+    std::vector<int32_t> janc, anchors;
+    int levels = 0;
+    std::vector<int32_t> aseg;
+    std::vector<hs::MPTree> trees;
+    std::vector<int32_t> lev;
+    std::vector<int2> kids;
+};
+
+// In joint order, with their segments.
+Anchors find_anchors(const hs_plan *plan, const Packing &pk)
+{
+    Anchors f;
+    build_anchors(plan, pk, f.janc, f.anchors, f.levels);
+    // Segments for the in-LDS anchor rounds: a cut before anchor k is valid
+    // when no anchor from k on points below k (anchors point to earlier
+    // anchors of their character); segments take the furthest valid cut
+    // within kAnchorSegCap anchors.  If some stretch has no valid cut that
+    // close, the rounds stay global.
+    const int64_t na = (int64_t)f.anchors.size();
+    std::vector<int64_t> sufmin((size_t)na + 1, INT64_MAX);
+    for (int64_t i = na - 1; i >= 0; --i) {
+        const int32_t pa = f.janc[f.anchors[i]];
+        sufmin[i] = std::min<int64_t>(sufmin[i + 1], pa < 0 ? INT64_MAX : pa);
+    }
+    f.aseg.push_back(0);
+    int64_t s = 0;
+    while (s < na) {
+        int64_t k = std::min<int64_t>(na, s + hs::kAnchorSegCap);
+        while (k > s && !(k == na || sufmin[k] >= k)) --k;
+        if (k == s) {
+            f.aseg.clear();
+            break;
+        }
+        f.aseg.push_back((int32_t)k);
+        s = k;
+    }
+    if (f.aseg.size() < 2 || f.levels <= 1) f.aseg.clear();
+    return f;
+}
+
+// What the forward's and the adjoint's set, of the same characters mostly,
+// have in common.
+struct AnchorTables {
+    std::vector<MPBlock> blocks;
+    Anchors found, planted;
+    bool tried = false, fits = false;  // planted
+
+    Anchors get(const hs_plan *plan, const Packing &pk, bool adjoint)
+    {
+        if (blocks.size() != pk.mpb.size() ||
+            std::memcmp(blocks.data(), pk.mpb.data(), blocks.size() * sizeof(MPBlock)) != 0) {
+            found = find_anchors(plan, pk);
+            blocks = pk.mpb;
+            tried = false;
+        }
+        // The anchors level by level, instead of in rounds: a level takes 0.3 us,
+        // a round over all anchors 25.  Rounds of segments in LDS are as quick
+        // downward, and upward too beyond some 48 levels if hardly two anchors
+        // send to the same one (a character of 57 blocks in a row: 24 against
+        // 35 us; 64 of them: 47 either way; 28 levels: 36 against 30).
+        bool plant = found.levels > 1 && found.levels <= hs::kTreeMaxLevels;
+        if (plant && !found.aseg.empty() && (!adjoint || found.levels > 48))
+            plant = adjoint && branched(found.janc, found.anchors);
+        if (!plant) return found;
+        if (!tried) {
+            tried = true;
+            planted = found;
+            planted.aseg.clear();
+            fits = plant_trees(pk, planted.janc, planted.anchors, planted.trees, planted.lev, planted.kids);
+        }
+        return fits ? planted : found;
+    }
+};
+
+hs_status make_mpset(MPSet &m, const hs_plan *plan, const Packing &pk, bool adjoint, AnchorTables &tables)
 {
     free_mpset(m);
     m.num_blocks = (int32_t)pk.mpb.size();
@@ -957,45 +1048,15 @@ hs_status make_mpset(MPSet &m, const hs_plan *plan, const Packing &pk, bool adjo
         }
     }
     if (pk.nmp == 0) return HS_OK;
-    std::vector<int32_t> janc, anchors;
-    build_anchors(plan, pk, janc, anchors, m.rounds);
+    Anchors f = tables.get(plan, pk, adjoint);
+    auto &[janc, anchors, levels, aseg, trees, lev, kids] = f;
     m.num_anchors = (int32_t)anchors.size();
-    std::vector<hs::MPTree> trees;
-    std::vector<int32_t> lev;
-    std::vector<int2> kids;
-    if (m.rounds > 0 && !plant_trees(pk, janc, anchors, trees, lev, kids)) trees.clear();
+    m.rounds = ceil_log2(levels);
+    m.num_aseg = aseg.empty() ? 0 : (int32_t)aseg.size() - 1;
     m.num_trees = (int32_t)trees.size();
     for (const hs::MPTree &t : trees) m.tree_anchors = std::max(m.tree_anchors, t.count);
     std::vector<int32_t> aself((size_t)pk.nmp, -1);
     for (size_t i = 0; i < anchors.size(); ++i) aself[anchors[i]] = (int32_t)i;
-    // Segments for the in-LDS anchor rounds: a cut before anchor k is valid
-    // when no anchor from k on points below k (anchors point to earlier
-    // anchors of their character); segments take the furthest valid cut
-    // within kAnchorSegCap anchors.  If some stretch has no valid cut that
-    // close, the rounds stay global.
-    std::vector<int32_t> aseg;
-    {
-        const int64_t na = (int64_t)anchors.size();
-        std::vector<int64_t> sufmin((size_t)na + 1, INT64_MAX);
-        for (int64_t i = na - 1; i >= 0; --i) {
-            const int32_t pa = janc[anchors[i]];
-            sufmin[i] = std::min<int64_t>(sufmin[i + 1], pa < 0 ? INT64_MAX : pa);
-        }
-        aseg.push_back(0);
-        int64_t s = 0;
-        while (s < na) {
-            int64_t k = std::min<int64_t>(na, s + hs::kAnchorSegCap);
-            while (k > s && !(k == na || sufmin[k] >= k)) --k;
-            if (k == s) {
-                aseg.clear();
-                break;
-            }
-            aseg.push_back((int32_t)k);
-            s = k;
-        }
-        if (aseg.size() < 2 || m.rounds == 0) aseg.clear();
-        m.num_aseg = aseg.empty() ? 0 : (int32_t)aseg.size() - 1;
-    }
     const size_t na = std::max<size_t>(1, anchors.size());
     std::vector<int32_t> e1(na, -1), none(na, -1), hfirst, hanc;
     for (size_t i = 0; i < anchors.size(); ++i) e1[i] = janc[anchors[i]];
@@ -1595,6 +1656,7 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
     plan->d_btiles = plan->d_bbig = nullptr;
     plan->d_bcode = nullptr;
     plan->num_btiles = plan->num_bbig = 0;
+    AnchorTables anchor_tables;
     {
         int64_t m_sync = 0;
         for (int64_t c = 0; c < plan->C; ++c) {
@@ -1650,7 +1712,7 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
         plan->d_bbig = at<TileDesc>(plan->d_adjoint, o_bbig);
         plan->d_bcode = at<int32_t>(plan->d_adjoint, o_bcode);
         plan->bwd_untiled = pb.nmp;
-        hs_status rc2 = make_mpset(plan->bmp, plan, pb, true);
+        hs_status rc2 = make_mpset(plan->bmp, plan, pb, true, anchor_tables);
         if (rc2 != HS_OK) return rc2;
     }
 
@@ -1659,7 +1721,7 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
     plan->d_tiles = nullptr;
     if ((err = upload(&plan->d_tiles, sorted)) != hipSuccess) return fail_hip(err, "hs_plan_create");
     plan->h_tiles = sorted;
-    hs_status rc = make_mpset(plan->mp, plan, pk, false);
+    hs_status rc = make_mpset(plan->mp, plan, pk, false, anchor_tables);
     if (rc != HS_OK) return rc;
     plan->max_units = pk.max_units;
     plan->shape = shape;

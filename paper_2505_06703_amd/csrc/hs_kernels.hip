@@ -3350,7 +3350,7 @@ mp_local_kernel(MPLaunch ml, PoseArgs pose)
 // composition an anchor and a barrier a level, where the rounds take a launch
 // each and, upward, atomics of hundreds of anchors on the few near the root.
 // Bound by the levels' latency (0.3 us each), so the plan takes it up to
-// kTreeMaxLevels levels.  24 characters of 3 500 to 30 000 branched joints (18
+// kTreeMaxLevels levels, or fewer where segments do as well.  24 characters of 3 500 to 30 000 branched joints (18
 // thousand anchors, 21 levels): 5 x 25 us of rounds upward became 18 us, the
 // downward half beside them; the adjoint call 165 -> 50 us.
 // dirs: 1 downward, 2 downward (even workgroups) and upward (odd ones).
@@ -4493,9 +4493,7 @@ hipError_t run_anchors(const MPLaunch &ml, bool both, const float4 **AP, hipStre
     // with no rounds the phase-1 products are final
     *AP = ml.A1;
     if (ml.num_anchors == 0) return hipSuccess;
-    // downward alone, rounds of pointer jumping in LDS are the quicker ones
-    // where the anchors are few enough
-    if (ml.num_trees > 0 && (both || ml.num_aseg == 0)) {
+    if (ml.num_trees > 0) {
         const int dirs = both ? 2 : 1;
         hipLaunchKernelGGL(mp_tree_kernel, dim3((unsigned)ml.num_trees * dirs), dim3(kTreeThreads),
                            tree_lds_bytes(ml.tree_anchors), stream, ml, dirs);
