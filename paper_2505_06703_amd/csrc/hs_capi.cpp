@@ -107,7 +107,8 @@ hipError_t upload(T **dst, const std::vector<T> &src)
 
 // Several tables or workspaces in one allocation, each 256-byte aligned: an
 // allocation costs a plan more than most tables' copies do.  add() and room()
-// return offsets for at(); what was added is copied by upload().
+// return offsets for at(); what was added is copied by upload(), in one copy
+// where it is small (a copy costs some 8 us of host time).
 struct Block {
     struct Table {
         const void *src;
@@ -133,6 +134,13 @@ struct Block {
         *dst = nullptr;
         if (size == 0) return hipSuccess;
         hipError_t err = hipMalloc(reinterpret_cast<void **>(dst), size);
+        size_t end = 0;
+        for (const Table &t : tables) end = std::max(end, t.offset + t.bytes);
+        if (err == hipSuccess && tables.size() > 1 && end <= (size_t)1 << 20) {
+            std::vector<char> stage(end, 0);
+            for (const Table &t : tables) std::memcpy(stage.data() + t.offset, t.src, t.bytes);
+            return hipMemcpy(*dst, stage.data(), end, hipMemcpyHostToDevice);
+        }
         for (const Table &t : tables)
             if (err == hipSuccess) err = hipMemcpy(*dst + t.offset, t.src, t.bytes, hipMemcpyHostToDevice);
         return err;
@@ -1391,11 +1399,23 @@ hs_status build_paths(hs_plan *plan)
     std::atomic<bool> fits{true};
     parallel_pieces(C, N, [&](int64_t b, int64_t e) {
         std::vector<int16_t> height, best, fan;
+        int64_t last = -1;
+        const int32_t *par = plan->h_parents.data();
         for (int64_t c = b; c < e && fits; ++c) {
             const int64_t o = off[c], n = off[c + 1] - o;
             if (n == 0 || n > hs::kMaxSyncTileJoints) continue;
-            pieces[c] = cut_paths(plan->h_parents.data() + o, plan->h_level.data() + o, n, lane.data() + o,
-                                  pos.data() + o, height, best, fan, losers[c]);
+            const int64_t l = last;
+            last = c;
+            if (l >= 0 && off[l + 1] - off[l] == n && std::memcmp(par + off[l], par + o, (size_t)n * sizeof(*par)) == 0) {
+                // one more of the same skeleton
+                std::copy_n(lane.data() + off[l], n, lane.data() + o);
+                std::copy_n(pos.data() + off[l], n, pos.data() + o);
+                pieces[c] = pieces[l];
+                losers[c] = losers[l];
+                continue;
+            }
+            pieces[c] = cut_paths(par + o, plan->h_level.data() + o, n, lane.data() + o, pos.data() + o, height, best,
+                                  fan, losers[c]);
             if (pieces[c] < 0 || pieces[c] > hs::kPathMaxLanes) fits = false;
         }
     });
