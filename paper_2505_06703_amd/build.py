@@ -15,7 +15,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIB_DIR, "libhs.so")
 SOURCES = [os.path.join(CSRC, "hs_kernels.hip"), os.path.join(CSRC, "hs_capi.cpp")]
-HEADERS = [os.path.join(CSRC, "hs_internal.h"), os.path.join(INCLUDE, "hs.h")]
+HEADERS = [os.path.join(CSRC, "hs_internal.h"), os.path.join(CSRC, "hs_ranges.h"), os.path.join(INCLUDE, "hs.h")]
 ARCH = "gfx950"
 
 

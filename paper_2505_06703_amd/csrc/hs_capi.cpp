@@ -3,6 +3,7 @@
 // HIP kernels in hs_kernels.hip.
 #include "hs.h"
 #include "hs_internal.h"
+#include "hs_ranges.h"
 
 #include <algorithm>
 #include <atomic>
@@ -49,50 +50,16 @@ hs_status fail_hip(hipError_t err, const char *what)
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-struct Range {
-    const void *p;
-    size_t bytes;
-    const char *name;
-};
-
-// A call's arrays, without an allocation (no call has more than a dozen).
-struct Ranges {
-    Range r[16];
-    size_t n = 0;
-    Ranges() = default;
-    Ranges(std::initializer_list<Range> list)
-    {
-        for (const Range &x : list) push_back(x);
-    }
-    void push_back(const Range &x)
-    {
-        if (n < 16) r[n++] = x;
-    }
-    size_t size() const { return n; }
-    const Range &operator[](size_t i) const { return r[i]; }
-    const Range *begin() const { return r; }
-    const Range *end() const { return r + n; }
-};
-
-bool overlap(const Range &a, const Range &b)
-{
-    if (!a.p || !b.p || a.bytes == 0 || b.bytes == 0) return false;
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a.p), b0 = reinterpret_cast<uintptr_t>(b.p);
-    return a0 < b0 + b.bytes && b0 < a0 + a.bytes;
-}
+using hs::Range;
+using hs::Ranges;
 
 // Every output must be disjoint from every input and from the other outputs.
 hs_status check_aliasing(const Ranges &outs, const Ranges &ins)
 {
-    for (size_t i = 0; i < outs.size(); ++i) {
-        for (const Range &in : ins)
-            if (overlap(outs[i], in))
-                return fail(HS_ERR_INVALID_ARG, "output %s overlaps input %s", outs[i].name, in.name);
-        for (size_t k = i + 1; k < outs.size(); ++k)
-            if (overlap(outs[i], outs[k]))
-                return fail(HS_ERR_INVALID_ARG, "outputs %s and %s overlap", outs[i].name, outs[k].name);
-    }
-    return HS_OK;
+    hs::Clash c;
+    if (!hs::find_clash(outs, ins, c)) return HS_OK;
+    if (c.input) return fail(HS_ERR_INVALID_ARG, "output %s overlaps input %s", c.out, c.other);
+    return fail(HS_ERR_INVALID_ARG, "outputs %s and %s overlap", c.out, c.other);
 }
 
 template <class T>
