@@ -255,10 +255,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# torch's own calls below torch.cuda.current_stream, if this version has them:
+# the Stream object in between is most of what a small call's stream costs
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
-    if stream is None and torch.cuda.is_initialized():
-        # the current device's current stream, without a Stream object for it
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if stream is None and _raw_stream and _raw_device and torch.cuda.is_initialized():
+        return _raw_stream(_raw_device())
     return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
