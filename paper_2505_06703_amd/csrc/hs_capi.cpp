@@ -2717,7 +2717,7 @@ hs_status sample_backward(const char *name, const hs_plan *plan, const hs_clip_l
     if (!dg.ok) return fail(HS_ERR_DEVICE, "%s: cannot select device", name);
     hs::SampleBwdArgs A{grad_quat, grad_trans, grad_key_quat, grad_key_trans, grad_time, grad_weight,
                         (int32_t)plan->C, reinterpret_cast<float4 *>(workspace)};
-    hipError_t err = hs::launch_pose_sample_backward(pa, A, stream);
+    hipError_t err = hs::launch_pose_sample_backward(pa, A, plan->ctx->num_cu, stream);
     if (err != hipSuccess) return fail_hip(err, name);
     return HS_OK;
 }

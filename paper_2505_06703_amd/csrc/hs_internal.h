@@ -393,7 +393,7 @@ struct SampleBwdArgs {
     // reads them instead of recomputing each reader's reverse step
     float4 *ws;
 };
-hipError_t launch_pose_sample_backward(const PoseArgs &pose, const SampleBwdArgs &A, hipStream_t stream);
+hipError_t launch_pose_sample_backward(const PoseArgs &pose, const SampleBwdArgs &A, int num_cu, hipStream_t stream);
 
 // The allocation-free route of the sampler's reverse mode keeps its
 // workspace ([N][2] float4) in a static device array of this many joints.

@@ -4592,7 +4592,7 @@ hipError_t launch_pose_sample(const TileLaunch &tl, const MPLaunch &ml, const Ch
     return hipSuccess;
 }
 
-hipError_t launch_pose_sample_backward(const PoseArgs &pose, const SampleBwdArgs &A, hipStream_t stream)
+hipError_t launch_pose_sample_backward(const PoseArgs &pose, const SampleBwdArgs &A, int num_cu, hipStream_t stream)
 {
     hipError_t err = hipSuccess;
     const bool keys = A.grad_key_quat || A.grad_key_trans;
@@ -4603,12 +4603,12 @@ hipError_t launch_pose_sample_backward(const PoseArgs &pose, const SampleBwdArgs
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if (keys) {
-        // two keys a workgroup where that leaves one for each of 256 CUs
-        // (whole gradient of the sampler and the scan, two keys against one:
-        // 64 clips of 30 keys 304 against 319 us, 30 clips 167 against 176,
-        // 16 clips 183 either way, 2 clips 442 against 313)
+        // two keys a workgroup where that leaves one for each CU (256 CUs, whole
+        // gradient of the sampler and the scan, two keys against one: 64
+        // clips of 30 keys 304 against 319 us, 30 clips 167 against 176, 16
+        // clips 183 either way, 2 clips 442 against 313)
         const int64_t pairs = (int64_t)pose.num_clips * ((pose.num_keys + 1) / 2);
-        const bool two = pairs >= 256;
+        const bool two = pairs >= num_cu;
         const int64_t blocks = two ? pairs : (int64_t)pose.num_clips * pose.num_keys;
         const auto kern = a.ws ? (two ? sample_bwd_keys_kernel<true, 2> : sample_bwd_keys_kernel<true, 1>)
                                : (two ? sample_bwd_keys_kernel<false, 2> : sample_bwd_keys_kernel<false, 1>);
