@@ -608,7 +608,9 @@ def measure(args, name):
                    "hip_graph": mode == "graph",
                    "input_sets": len(w.sets),
                    **({"adjoint": args.adjoint,
-                       "adjoint_blocks_per_wave": info["adjoint_blocks_per_wave"]} if diff else {})},
+                       # of the two-level kernel, which the step of this size takes when asked to
+                       "adjoint_blocks_per_wave": info["adjoint_blocks_per_wave"]
+                       if args.adjoint == "anchors" else None} if diff else {})},
         "roofline": roof,
         "launch_modes": launch,
     }

@@ -224,8 +224,8 @@ typedef struct hs_plan_info {
     int32_t max_block_chain;   /* longest chain of 64-joint blocks on any path */
     int32_t schedule;          /* HS_SCHED_QUEUE or HS_SCHED_CLASSES: the forward's launches */
     int32_t max_anchors;       /* queue: most anchors of one tile (LDS slots), else 0 */
-    int32_t adjoint_blocks_per_wave; /* two-level adjoint of hs_effector_step: 64-joint blocks
-                                  per wave (0: the plan has no such tiles) */
+    int32_t adjoint_blocks_per_wave; /* two-level adjoint of hs_effector_step, where that kernel
+                                  runs: 64-joint blocks per wave (0: the plan has no such tiles) */
     int64_t chain_joints;      /* multipass joints of chain characters (every parent the previous
                                   joint), scanned in one pass over their poses */
 } hs_plan_info;

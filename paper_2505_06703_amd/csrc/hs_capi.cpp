@@ -1147,16 +1147,11 @@ std::vector<int> all_tile_codes(const hs_plan *plan, const std::vector<TileDesc>
     return na;
 }
 
-// The path adjoint's tiles (hs_internal.h, PathTile): every character of up
-// to kMaxSyncTileJoints joints in pieces of paths.  A path goes from its head
-// to the child with the most levels below it, so that the longest paths stay
-// whole, and is cut every kPathLen joints.  Builds nothing where some
-// character has more than kPathMaxLanes pieces (a thread each) or a joint more
-// than kPathMaxFanIn pieces below it (one thread adds them): stars and the
-// like, where few rounds of the synchronous kernel do.
 // The pieces of one character (parents pa, n joints): each joint's piece,
-// counted from 0, and its place in it.  Returns their number, or -1 when too
-// many lie below one joint.
+// counted from 0, and its place in it.  A path goes from its head to the child
+// with the most levels below it, so that the longest paths stay whole, and is
+// cut every kPathLen joints.  Returns the pieces' number, or -1 when too many
+// lie below one joint.
 // `losers`: the sends of the synchronous rounds that find their receiver taken.
 // Round r has a sender for each joint at least 2^r levels below the top and a
 // receiver for each at least 2^r above the lowest joint below it.
@@ -1352,6 +1347,12 @@ void choose_paths(hs_plan *plan, const std::vector<double> &jump, const std::vec
     P.use[2] = !plan->b_anchor_ok || (!plan->b_one_round[2] && threads <= 0.6);
 }
 
+// The path adjoint's tiles (hs_internal.h, PathTile): every character of up to
+// kMaxSyncTileJoints joints in pieces of paths.  Builds nothing where some
+// character has more than kPathMaxLanes pieces (a thread each) or a joint more
+// than kPathMaxFanIn pieces below it (one thread adds them): stars and the
+// like, where few rounds of the synchronous kernel do; nor where the other
+// kernels are expected to be the quicker for every kind of seed.
 hs_status build_paths(hs_plan *plan)
 {
     auto &P = plan->paths;
@@ -1633,10 +1634,11 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
     const int max_chain_tiles = pk.max_chain_tiles, max_chain_mp = pk.max_chain_mp;
 
     // The adjoint gets tiles of its own.  Characters of up to 1024 joints go
-    // to the synchronous-round kernel, on tiles just large enough for the
-    // largest of them but at least 256 joints (4 waves: many workgroups per
-    // CU; measured against 512 joints: 179 vs 195 us on 10 000 x 256 joints,
-    // 12 vs 20 us on 64 x 64); characters of up to 1664 joints to the
+    // to the synchronous-round or the two-level kernel, on tiles just large
+    // enough for the largest of them but at least 256 joints (4 waves: many
+    // workgroups per CU; measured against 512 joints: 179 vs 195 us on 10 000 x
+    // 256 joints, 12 vs 20 us on 64 x 64), or to the path adjoint, which has
+    // tiles of its own (build_paths); characters of up to 1664 joints to the
     // dataflow kernel; the rest to the multipass adjoint.
     (void)hipFree(plan->d_adjoint);
     plan->d_adjoint = nullptr;

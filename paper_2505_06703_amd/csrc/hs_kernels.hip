@@ -2142,16 +2142,19 @@ const void *anchor_kernel_of(int seed)
 // What bounds it: the latency of one tile's phases (45 thousand clocks, of
 // which a wave issues for 8), with the arithmetic of the walks (five
 // compositions a joint) and HBM behind it.  Four joints a lane keep the local
-// transforms and adjoints of a lane in 166 registers, three waves a SIMD; with
+// transforms and adjoints of a lane in up to 166 registers (dense seeds spill 20
+// bytes), three waves a SIMD; with
 // eight (two waves) 2048 characters of 32 to 1024 joints took 75 us instead of
 // 62, 1024 x 512 joints 27.0 instead of 25.4.  The one LDS array, 48 bytes a
 // joint, turns joint order (coalesced loads and stores) into lanes and back,
 // and holds the lanes' arrays in between.  Senders' rows planned ahead instead
 // of lists built with LDS exchanges (dozens of lanes reach one lane on bushy
-// trees, a round trip each): 62 -> 54 us there.  Against the synchronous
-// rounds: 2048 x 32..1024 joints 118 -> 54 us, 10 000 x 256 joints 170 -> 92 us
+// trees, a round trip each): 62 -> 54 us there.  A lane of one joint costs
+// as much as one of four, and the busiest lane adds its senders one after the
+// other, so bushy trees gain least and some lose (choose_paths in hs_capi.cpp).
+// Against the synchronous rounds: 2048 x 32..1024 joints 118 -> 54 us, 10 000 x 256 joints 170 -> 92 us
 // (its 307 MB need 60 us at the rate of a copy); against the two-level kernel,
-// end-effector steps of 1024 x 512 joints 33.7 -> 25.8 us.
+// end-effector steps of 1024 x 512 joints 33.7 -> 25.0 us.
 //
 // LDS: rows [max_rows][3] f4, or in their place Mx [lanes][3] f4 (first the
 // branches' products), Cx [lanes][3] f4 and ax [lanes] int | slots [max_count]
@@ -4483,8 +4486,6 @@ hipError_t launch_forward_tiles(const TileLaunch &tl, const PoseArgs &pose, cons
                   : launch_fwd_tiles_w<false, 0>(tl, pose, out, stream);
 }
 
-// Phase 1 per block, anchor rounds, final pass; Gc non-NULL: compact global
-// transforms for the adjoint instead of the outputs.
 // The anchors' transforms from their phase-1 products (A1), into *AP; both:
 // the adjoint's sums over the anchors too, from H into S[0], where the trees do
 // them in the same launch.
@@ -4519,6 +4520,7 @@ hipError_t run_anchors(const MPLaunch &ml, bool both, const float4 **AP, hipStre
     return hipSuccess;
 }
 
+// The forward: phase 1 per block, the anchors, final pass.
 hipError_t run_multipass(const MPLaunch &ml, const PoseArgs &pose, const OutArgs &out, hipStream_t stream)
 {
     const dim3 blk(kMPWaves * kWave);
