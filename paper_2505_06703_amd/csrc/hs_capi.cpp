@@ -976,37 +976,36 @@ Anchors find_anchors(const hs_plan *plan, const Packing &pk)
     return f;
 }
 
-// What the forward's and the adjoint's set, of the same characters mostly,
-// have in common.
+// The anchors for the forward's set and then for the adjoint's, of the same
+// characters mostly.
 struct AnchorTables {
     std::vector<MPBlock> blocks;
-    Anchors found, planted;
-    bool tried = false, fits = false;  // planted
+    Anchors a;
+    bool planted = false, refused = false;
 
-    Anchors get(const hs_plan *plan, const Packing &pk, bool adjoint)
+    Anchors &get(const hs_plan *plan, const Packing &pk, bool adjoint)
     {
         if (blocks.size() != pk.mpb.size() ||
             std::memcmp(blocks.data(), pk.mpb.data(), blocks.size() * sizeof(MPBlock)) != 0) {
-            found = find_anchors(plan, pk);
+            a = find_anchors(plan, pk);
             blocks = pk.mpb;
-            tried = false;
+            planted = refused = false;
         }
         // The anchors level by level, instead of in rounds: a level takes 0.3 us,
         // a round over all anchors 25.  Rounds of segments in LDS are as quick
         // downward, and upward too beyond some 48 levels if hardly two anchors
         // send to the same one (a character of 57 blocks in a row: 24 against
-        // 35 us; 64 of them: 47 either way; 28 levels: 36 against 30).
-        bool plant = found.levels > 1 && found.levels <= hs::kTreeMaxLevels;
-        if (plant && !found.aseg.empty() && (!adjoint || found.levels > 48))
-            plant = adjoint && branched(found.janc, found.anchors);
-        if (!plant) return found;
-        if (!tried) {
-            tried = true;
-            planted = found;
-            planted.aseg.clear();
-            fits = plant_trees(pk, planted.janc, planted.anchors, planted.trees, planted.lev, planted.kids);
+        // 35 us; 64 of them: 47 either way; 28 levels: 36 against 30).  What the
+        // forward plants, having no segments, the adjoint would too.
+        bool plant = a.levels > 1 && a.levels <= hs::kTreeMaxLevels && !planted && !refused;
+        if (plant && !a.aseg.empty() && (!adjoint || a.levels > 48)) plant = adjoint && branched(a.janc, a.anchors);
+        if (plant) {
+            planted = plant_trees(pk, a.janc, a.anchors, a.trees, a.lev, a.kids);
+            refused = !planted;
+            if (planted) a.aseg.clear();
+            else a.trees.clear();
         }
-        return fits ? planted : found;
+        return a;
     }
 };
 
@@ -1023,8 +1022,7 @@ hs_status make_mpset(MPSet &m, const hs_plan *plan, const Packing &pk, bool adjo
         }
     }
     if (pk.nmp == 0) return HS_OK;
-    Anchors f = tables.get(plan, pk, adjoint);
-    auto &[janc, anchors, levels, aseg, trees, lev, kids] = f;
+    auto &[janc, anchors, levels, aseg, trees, lev, kids] = tables.get(plan, pk, adjoint);
     m.num_anchors = (int32_t)anchors.size();
     m.rounds = ceil_log2(levels);
     m.num_aseg = aseg.empty() ? 0 : (int32_t)aseg.size() - 1;
@@ -1645,7 +1643,9 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
     plan->d_btiles = plan->d_bbig = nullptr;
     plan->d_bcode = nullptr;
     plan->num_btiles = plan->num_bbig = 0;
-    AnchorTables anchor_tables;
+    AnchorTables anchor_tables;  // the adjoint's set comes last: it renames them
+    hs_status rc = make_mpset(plan->mp, plan, pk, false, anchor_tables);
+    if (rc != HS_OK) return rc;
     {
         int64_t m_sync = 0;
         for (int64_t c = 0; c < plan->C; ++c) {
@@ -1701,8 +1701,7 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
         plan->d_bbig = at<TileDesc>(plan->d_adjoint, o_bbig);
         plan->d_bcode = at<int32_t>(plan->d_adjoint, o_bcode);
         plan->bwd_untiled = pb.nmp;
-        hs_status rc2 = make_mpset(plan->bmp, plan, pb, true, anchor_tables);
-        if (rc2 != HS_OK) return rc2;
+        if ((rc = make_mpset(plan->bmp, plan, pb, true, anchor_tables)) != HS_OK) return rc;
     }
 
     hipError_t err;
@@ -1710,8 +1709,6 @@ hs_status build_tables(hs_plan *plan, const Shape &shape, int strategy)
     plan->d_tiles = nullptr;
     if ((err = upload(&plan->d_tiles, sorted)) != hipSuccess) return fail_hip(err, "hs_plan_create");
     plan->h_tiles = sorted;
-    hs_status rc = make_mpset(plan->mp, plan, pk, false, anchor_tables);
-    if (rc != HS_OK) return rc;
     plan->max_units = pk.max_units;
     plan->shape = shape;
 
