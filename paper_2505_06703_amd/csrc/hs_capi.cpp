@@ -1286,7 +1286,7 @@ double fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e
 // Which seeds the path adjoint serves.  It has a third of the other kernels'
 // work on trees of long paths, but a tile takes it longer where there is little
 // to jump over, or many pieces below one, and a piece of one joint costs a
-// thread all the same.  Fitted to 270 batches of chains, random trees, k-ary
+// thread all the same.  Fitted to 370 batches of chains, random trees, k-ary
 // trees, stars and humanoids of 5 to 1000 joints, 5 to 2 000 000 in all.
 //
 // Dense seeds: with more than four tiles of the synchronous rounds for each CU
@@ -1298,7 +1298,7 @@ double fill_path_tile(const hs_plan *plan, hs::PathTile &t, int64_t c, int64_t e
 // CU.  The path adjoint's: what fill_path_tile returned, and its waves.  Both
 // are within 15 % of the measured times mostly, and so is the call of the better
 // kernel's (64 x 1000-joint trees: paths 20 against 57 us; 1000 stars of 60: 17
-// against 9; 200 humanoids of 256 joints: 12.7 against 10.7).
+// against 9; 256 humanoids of 256 joints: 12.7 against 10.7).
 //
 // End-effector seeds: the two-level kernel while all its tiles are resident
 // at once (200 x 512 joints: 16.3 against 18.3 us), and beyond that where the
